@@ -147,17 +147,14 @@ def _bias(c):
 
 
 def _share(c):
-    """(pairs on this rank, experts with rows), estimated over a sample of at most 1024 tokens."""
+    """(pairs on this rank, experts with rows), from a sample of at most 1024 tokens."""
     El, _ = _slice(c)
-    if El == c["E"] and not c["zipf"]:
-        return c["T"] * c["k"], c["E"] * (1 - (1 - c["k"] / c["E"]) ** c["T"])
     n = min(c["T"], 1024)
     lg = np.random.default_rng(7).standard_normal((n, c["E"]), np.float32) + _bias(c)
     ids = np.argpartition(-lg, c["k"] - 1, axis=1)[:, :c["k"]]
     e0 = c["rank"] * El if c["layout"] == "ep" else 0
     cnt = np.bincount(ids.ravel(), minlength=c["E"])[e0:e0 + El]
-    active = float(np.sum(1 - (1 - np.minimum(cnt, n) / n) ** c["T"]))
-    return max(1, int(cnt.sum() * c["T"] / n)), max(1.0, active)
+    return max(1, int(cnt.sum() * c["T"] / n)), max(1, int(np.sum(cnt > 0)))
 
 
 def _rows(c):
