@@ -253,7 +253,7 @@ extern "C" moe_status moe_grouped_ffn_shared(const uint16_t *x, int64_t x_rows, 
             return fail(MOE_ERR_UNSUPPORTED, "%s: n_local_experts + 1 exceeds %d", fn, MOE_MAX_EXPERTS);
         if (cap_rows + shared_count >= ((int64_t)1 << 31))
             return fail(MOE_ERR_UNSUPPORTED, "%s: cap_rows + shared_count too large", fn);
-        if (!ffn_large_tiles(x_rows, cap_rows + shared_count, H, I_s))
+        if (!ffn_whole_slices(H, I_s) || !ffn_large_tiles(x_rows, cap_rows + shared_count, H, I_s))
             return fail(MOE_ERR_UNSUPPORTED,
                         "%s: H=%d and I_s=%d must be multiples of 64, from 128 to 2^26, with operands under 4 GiB",
                         fn, H, I_s);
@@ -309,7 +309,7 @@ extern "C" moe_status moe_layer_forward(const uint16_t *x, const float *logits, 
             return fail(MOE_ERR_UNSUPPORTED, "%s: n_local_experts + 1 exceeds %d", fn, MOE_MAX_EXPERTS);
         if (cap + shared_count >= ((int64_t)1 << 31))
             return fail(MOE_ERR_UNSUPPORTED, "%s: cap_rows + shared_count too large", fn);
-        if (!ffn_large_tiles(T, cap + shared_count, H, I_s))
+        if (!ffn_whole_slices(H, I_s) || !ffn_large_tiles(T, cap + shared_count, H, I_s))
             return fail(MOE_ERR_UNSUPPORTED,
                         "%s: H=%d and I_s=%d must be multiples of 64, from 128 to 2^26, with operands under 4 GiB",
                         fn, H, I_s);

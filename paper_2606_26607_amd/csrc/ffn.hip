@@ -21,7 +21,7 @@
 namespace moe {
 namespace {
 
-constexpr int BM = 64, BN = 64, BK = 64;  // the general kernel (any K multiple of 8)
+constexpr int BM = 64, BN = 64, BK = 64;  // the general kernel (operands past 32-bit byte offsets)
 constexpr int KCH = BK / 8;               // 16-byte chunks per tile row
 
 __device__ __forceinline__ int64_t clamp_row(int32_t v, int64_t cap)
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(const uint16_t *__restrict__ 
 
 
 // ---------------------------------------------------------------------------
-// Large-tile kernel (K a multiple of 64, at least 128): BMxBN tiles (BN counts
+// Large-tile kernel (K any multiple of 8): BMxBN tiles (BN counts
 // weight rows; a gated tile holds BN/2 gate rows and the BN/2 matching up
 // rows), 8 waves (two per SIMD) in a WM x (8/WM) grid, each wave owning
 // (BM/WM)x(BN*WM/8) of 32x32x16 MFMA blocks, accumulators in AGPRs.
@@ -606,6 +606,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(const uint16_t *__restrict__ 
 // coalesced 16-byte stores.
 // ---------------------------------------------------------------------------
 constexpr int BIG_BK = 64;        // K per slice
+
+// K-slices of a reduction of length K (a multiple of 8): the last one may be
+// partly past K.
+__host__ __device__ __forceinline__ int k_slices(int K) { return (K + BIG_BK - 1) / BIG_BK; }
 constexpr int CPR = BIG_BK / 8;   // 16-byte chunks per LDS row
 constexpr int RPI = 64 / CPR;     // rows per DMA instruction
 static_assert(RPI == 8, "a lane's DMA row is lane / 8");
@@ -984,7 +988,7 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
     const int wm = wave / WN, wn = wave % WN;
     const int n_tiles = (N + OUTN - 1) / OUTN;
-    const int nk = K / BIG_BK;
+    const int nk = k_slices(K);
     // the class runs on grp_size workgroups; this one is number v of them
     // (negative: not one of them).  deal (small-row class only): whole tiles
     // dealt round robin over the group instead of stream-K
@@ -1153,6 +1157,25 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
             for (int q = 0; q < B_INS; ++q) src.vob[q] = b_off(q, wave * B_INS + q);
         }
 
+        // A last slice partly past K: its chunks at or past K would read the
+        // next row's first values.  Before its loads go out, the lanes that
+        // carry such a chunk take the offset num_records, so they read zeros
+        // (of both operands: a zero times the other's infinity would be NaN).
+        // The general kernel served these widths before: gate-up and down of
+        // the Qwen-MoE-shaped TP slice (I_s = 96, 2051 tokens) 148 + 52 ->
+        // 57 + 50 us, of 96 experts of H = 3608, I_s = 480 (1656 tokens)
+        // 537 + 214 -> 250 + 134 us.
+        // It is the last slice issued for the tile, so the offsets are changed
+        // in place; tail is its local index in this piece (-1: none).
+        const int k_left = K - (nk - 1) * BIG_BK;
+        const int tail = k_left < BIG_BK ? nk - 1 - klo : -1;
+        auto mask_tail = [&](uint32_t (&off)[8], int n, int g0, int num_records) {
+            const int c0 = (lane & 7) ^ (lane >> 3);  // chunk of an even instruction; an odd one's is c0 ^ 1
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (q < n && ((c0 ^ ((g0 + q) & 1)) * 8 >= k_left)) off[q] = (uint32_t)num_records;
+        };
+
         f32x16_t acc[MB][NB];
 #pragma unroll
         for (int i = 0; i < MB; ++i)
@@ -1174,14 +1197,19 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
         using F_ = std::false_type;
         if constexpr (ROLES) {
             // prologue: A(0) on the A loaders, B(0) and B(1) on the B loaders
+            // (NI is even, so instruction q's parity is q's)
+            auto mask_own = [&]() { mask_tail(src.voa, NI, 0, src.ra.z); };
             if (loads_a) {
+                if (tail == 0) mask_own();
 #pragma unroll
                 for (int q = 0; q < NI; ++q) issue_own<NI>(src, a_slot(0), kof(0), q);
                 asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             } else {
+                if (tail == 0) mask_own();
 #pragma unroll
                 for (int q = 0; q < NI; ++q) issue_own<NI>(src, b_slot(0), kof(0), q);
                 if (ns > 1) {
+                    if (tail == 1) mask_own();
 #pragma unroll
                     for (int q = 0; q < NI; ++q) issue_own<NI>(src, b_slot(1), kof(1), q);
                     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NI) : "memory");
@@ -1228,15 +1256,26 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
                 __builtin_amdgcn_sched_barrier(0);
             };
             int s = 0;
-            for (; s + 2 < ns; ++s) slice(s, T_{}, T_{});
-            for (; s + 1 < ns; ++s) slice(s, T_{}, F_{});
+            for (; s + 2 < ns; ++s) {
+                if (!loads_a && s + 2 == tail) mask_own();
+                slice(s, T_{}, T_{});
+            }
+            for (; s + 1 < ns; ++s) {
+                if (loads_a && s + 1 == tail) mask_own();
+                slice(s, T_{}, F_{});
+            }
             for (; s < ns; ++s) slice(s, F_{}, F_{});
         } else {
             // prologue: B(0), then (A(t), B(t+1)) for t < LA; wait for A(0), B(0)
+            auto mask_a = [&]() { mask_tail(src.voa, A_INS, wave * A_INS, src.ra.z); };
+            auto mask_b = [&]() { mask_tail(src.vob, B_INS, wave * B_INS, src.rb.z); };
+            if (tail == 0) mask_b();
     #pragma unroll
             for (int q = 0; q < B_INS; ++q) issue_b<BNt, STREAM>(src, b_slot(0), kof(0), q);
     #pragma unroll
             for (int t = 0; t < LA; ++t) {
+                if (t == tail) mask_a();
+                if (t + 1 == tail) mask_b();
                 if (t < ns) {
     #pragma unroll
                     for (int q = 0; q < A_INS; ++q) issue_a<BMt>(src, a_slot(t), kof(t), q);
@@ -1288,8 +1327,14 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
                 __builtin_amdgcn_sched_barrier(0);
             };
             int s = 0;
-            for (; s + LA + 1 < ns; ++s) slice(s, T_{}, T_{});
-            for (; s + LA < ns; ++s) slice(s, T_{}, F_{});
+            for (; s + LA + 1 < ns; ++s) {
+                if (s + LA + 1 == tail) mask_b();
+                slice(s, T_{}, T_{});
+            }
+            for (; s + LA < ns; ++s) {
+                if (s + LA == tail) mask_a();
+                slice(s, T_{}, F_{});
+            }
             for (; s < ns; ++s) slice(s, F_{}, F_{});
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1580,7 +1625,7 @@ void gemm_grouped(GemmArgs g, TileClass small, TileClass large, int tslot)
     const int64_t n_tiles = (g.N + OUTN - 1) / OUTN;
     const bool tall = small.tile_prefix[g.ne + 1] == SMALL128.rows;  // uniform
     const SmallGroup sg = small_group((int64_t)large.tile_prefix[g.ne] * n_tiles,
-                                      (int64_t)small.tile_prefix[g.ne] * n_tiles, g.K / BIG_BK, gridDim.x,
+                                      (int64_t)small.tile_prefix[g.ne] * n_tiles, k_slices(g.K), gridDim.x,
                                       tall ? SMALL128 : SMALL64, vx);
     if (tall)
         gemm_class<SMALL128.rows, BIGN, GATED, SMALL_WM, true, S128_ASL, S128_BSL, STREAM>(
@@ -1617,7 +1662,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void splitk_reduce(const int32_t *__r
     constexpr int OUTN = GATED ? BIGN / 2 : BIGN;
     constexpr int JJ = GATED ? NB / 2 : NB;  // output blocks per wave row
     const int n_tiles = (N + OUTN - 1) / OUTN;
-    const int nk = K / BIG_BK;
+    const int nk = k_slices(K);
     const WorkSplit ws((int64_t)tile_prefix[ne] * n_tiles, nk, G, SPLIT_AUTO);
     const int64_t items = (ws.T - ws.dp) * MB * JJ;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1840,7 +1885,7 @@ int device_cus()
 // small-row plans.
 SchedShape sched_shape(int H, int Is, int grid)
 {
-    SchedShape sh{(int)ceil_div(Is, BIGN / 2), H / BIG_BK, (int)ceil_div(H, BIGN), Is / BIG_BK, grid, {}, {}};
+    SchedShape sh{(int)ceil_div(Is, BIGN / 2), k_slices(H), (int)ceil_div(H, BIGN), k_slices(Is), grid, {}, {}};
     const int nk[2] = {sh.nk_gu, sh.nk_dn};
     const SmallKind kinds[2] = {SMALL64, SMALL128};
     for (int gi = 0; gi < 2; ++gi)
@@ -1860,6 +1905,10 @@ SchedShape sched_shape(int H, int Is, int grid)
 //   h [cap, I_s] bf16
 // The two GEMMs run one after the other on the stream and share the partial
 // slots; each keeps its own tile counters.
+// Widths the large-tile kernels serve (multiples of 8, which every entry
+// point checks): small enough that a row's offsets and the tile numbers fit.
+bool ffn_widths(int H, int Is) { return H <= (1 << 26) && Is <= (1 << 26); }
+
 struct FfnLayout {
     bool big;
     int64_t t_gu, t_dn, ts_gu, ts_dn;  // tile-count bounds per class and GEMM
@@ -1868,7 +1917,7 @@ struct FfnLayout {
         off_h, total;
     FfnLayout(int64_t cap, int El, int H, int Is)
     {
-        big = (H % BIG_BK == 0) && (Is % BIG_BK == 0) && H >= 2 * BIG_BK && Is >= 2 * BIG_BK;
+        big = ffn_widths(H, Is);
         const int bm = big ? BIGM : BM;
         const int64_t mt = ceil_div(cap, bm) + El;
         t_gu = mt * ceil_div(Is, big ? BIGN / 2 : BN);
@@ -1906,12 +1955,10 @@ size_t ffn_workspace_bytes(int64_t cap, int El, int H, int Is)
 
 bool ffn_large_tiles(int64_t x_rows, int64_t rows, int H, int Is)
 {
-    // K a multiple of 64 with at least two slices, every operand
-    // addressable with 32-bit buffer offsets, and small-row tile numbers
-    // below 2^31 (at most 2 * 1025 + 28 m-tiles, with a shared expert, of
-    // 2^26 / 128 + 1 n-tiles)
-    if (H % BIG_BK || Is % BIG_BK || H < 2 * BIG_BK || Is < 2 * BIG_BK) return false;
-    if (H > (1 << 26) || Is > (1 << 26)) return false;
+    // every operand addressable with 32-bit buffer offsets, and small-row
+    // tile numbers below 2^31 (at most 2 * 1025 + 28 m-tiles, with a shared
+    // expert, of 2^26 / 128 + 1 n-tiles)
+    if (!ffn_widths(H, Is)) return false;
     const int64_t lim = ((int64_t)1 << 32) - 4 * (int64_t)(H > Is ? H : Is);
     return x_rows * (int64_t)H * 2 < lim && rows * (int64_t)H * 2 < lim && rows * (int64_t)Is * 2 < lim;
 }
@@ -1982,7 +2029,7 @@ hipError_t launch_gemms(const FfnCall &c, const uint16_t *x, int64_t x_rows, con
                     g, sm, lg, device_ts_slot(MOE_K_GATE_UP));
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
-        if (H / BIG_BK >= SPLIT_MIN_NK) {  // the large tiles may have been split over K
+        if (k_slices(H) >= SPLIT_MIN_NK) {  // the large tiles may have been split over K
             KernelTimer timer(MOE_K_SPLITK_REDUCE, s);
             splitk_reduce<true><<<dim3(REDUCE_GRID), dim3(GEMM_THREADS), 0, s>>>(
                 offsets, c.split, c.pre, El, ne, cap, sc, Is, H, L.grid, c.part, c.h, c.h_sh);
@@ -2001,7 +2048,7 @@ hipError_t launch_gemms(const FfnCall &c, const uint16_t *x, int64_t x_rows, con
                     g, sm, lg, device_ts_slot(MOE_K_DOWN));
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
-        if (Is / BIG_BK >= SPLIT_MIN_NK) {
+        if (k_slices(Is) >= SPLIT_MIN_NK) {
             KernelTimer timer(MOE_K_SPLITK_REDUCE, s);
             splitk_reduce<false><<<dim3(REDUCE_GRID), dim3(GEMM_THREADS), 0, s>>>(
                 offsets, c.split_d, c.pre_ld, El, ne, cap, sc, H, Is, L.grid, c.part, y, shared_y);
@@ -2094,7 +2141,7 @@ bool layer_fused_prep(int64_t T, int k, int El, int H, int Is, int64_t sc)
     const int64_t npairs = T * k, cap = T * (k < El ? k : El);
     int nbits = 0;
     while ((1 << nbits) < El + 2) ++nbits;
-    const bool fuse = npairs > 0 && El <= 64 && El + (sc > 0 ? 1 : 0) <= LAYER_NE_MAX &&
+    const bool fuse = npairs > 0 && El <= 64 && El + (sc > 0 ? 1 : 0) <= LAYER_NE_MAX && ffn_whole_slices(H, Is) &&
                       ffn_large_tiles(T, cap + sc, H, Is);
     const bool small = npairs <= permute_dev::SMALL_PAIRS && npairs * (nbits + 2) <= LAYER_SMALL_WORK;
     return fuse && (small || permute_chunks(T, k, El) <= permute_dev::SCAN_SCATTER_MAX_CHUNKS);

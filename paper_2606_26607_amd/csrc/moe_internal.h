@@ -62,8 +62,11 @@ hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, 
                           hipStream_t s);
 
 size_t ffn_workspace_bytes(int64_t cap, int El, int H, int Is);
-// Whether the 64-wide-K large-tile kernels serve these sizes (x_rows: rows of
-// the activation operand; rows: all rows of the call).  A call with a shared
+// Widths made of whole 64-wide K-slices, two at least: what a shared expert's
+// call takes and what moe_layer_forward's fused first launches serve.
+inline bool ffn_whole_slices(int H, int Is) { return H % 64 == 0 && Is % 64 == 0 && H >= 128 && Is >= 128; }
+// Whether the large-tile kernels serve these sizes (x_rows: rows of the
+// activation operand; rows: all rows of the call).  A call with a shared
 // expert needs them.
 bool ffn_large_tiles(int64_t x_rows, int64_t rows, int H, int Is);
 // shared_rows = 0: no shared expert (sw13, sw2, shared_y unused).

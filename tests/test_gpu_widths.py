@@ -1,0 +1,79 @@
+"""Widths that are not whole 64-wide K-slices (needs an MI355X): the last
+slice of either GEMM is partly past K, and its loads read zeros there.  Every
+case is checked against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import moe_inputs as mi
+import paper_2606_26607_amd as moe
+from tests.util import assert_close_rel, bf16_f64, dev_bf16, host_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    moe.lib()
+
+
+# rows per expert: whole and partial 256-row tiles, 64- and 128-row ones, single rows, none
+ROWS = [300, 0, 64, 120, 1, 513, 17]
+
+
+@pytest.mark.parametrize("H,Is", [(8, 8),         # one slice of one chunk on both sides
+                                  (56, 72),       # one slice; one chunk past a slice
+                                  (128, 120),     # whole slices; a slice short of one chunk
+                                  (136, 96), (1000, 328),
+                                  (264, 8248)])   # a split K whose last slice is partial
+@pytest.mark.parametrize("gather", [False, True])
+def test_partial_last_slice(oracle, H, Is, gather):
+    El, k, n = len(ROWS), 2, sum(ROWS)
+    offs = np.concatenate([[0], np.cumsum(ROWS)]).astype(np.int32)
+    T = n if not gather else 600
+    x = mi.random_bf16((T, H), seed=H, tag=70)
+    # values past K would be the next row's: make them large, so that one read by mistake shows
+    x[:, 0] = mi.f32_to_bf16_bits(np.full(T, 50.0, np.float32))
+    w13 = mi.random_bf16((El, 2 * Is, H), seed=H, tag=71, std=0.05)
+    w2 = mi.random_bf16((El, H, Is), seed=H, tag=72, std=0.05)
+    r2p = np.random.default_rng(H).integers(0, T * k, n).astype(np.int32) if gather else None
+    y = moe.grouped_ffn(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2),
+                        row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1)
+    torch.cuda.synchronize()
+    ref = oracle.grouped_ffn(x if r2p is None else x[r2p // k], offs, w13, w2)
+    assert_close_rel(bf16_f64(host_bf16(y)), ref, what=f"H={H} Is={Is} gather={gather}")
+
+
+def test_infinite_neighbour(oracle):
+    """A row's neighbour in memory holds infinities: they stay out of the row's own result."""
+    H, Is, n = 200, 72, 300
+    x = mi.random_bf16((n, H), seed=5, tag=73)
+    x[1::2, :8] = mi.f32_to_bf16_bits(np.array([np.inf], np.float32))[0]
+    w13 = mi.random_bf16((1, 2 * Is, H), seed=5, tag=74, std=0.05)
+    w2 = mi.random_bf16((1, H, Is), seed=5, tag=75, std=0.05)
+    offs = np.array([0, n], np.int32)
+    y = moe.grouped_ffn(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2))
+    torch.cuda.synchronize()
+    got = bf16_f64(host_bf16(y))[0::2]
+    ref = oracle.grouped_ffn(x[0::2], np.array([0, len(got)], np.int32), w13, w2)
+    assert_close_rel(got, ref, what="rows beside infinite ones")
+
+
+def test_operand_beyond_4gib(oracle):
+    """A token matrix past what 32-bit byte offsets address takes the general kernels; the rows read lie at its
+    far end."""
+    T, H, Is = (1 << 32) // (2 * 8192) + 600, 8192, 64
+    x = torch.empty((T, H), dtype=torch.bfloat16, device="cuda")
+    x[-500:] = dev_bf16(mi.random_bf16((500, H), seed=6, tag=76))
+    w13 = mi.random_bf16((2, 2 * Is, H), seed=6, tag=77, std=0.02)
+    w2 = mi.random_bf16((2, H, Is), seed=6, tag=78, std=0.05)
+    r2p = (np.random.default_rng(6).integers(T - 500, T, 130)).astype(np.int32)
+    offs = np.array([0, 100, 130], np.int32)
+    y = moe.grouped_ffn(x, torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2),
+                        row_to_pair=torch.from_numpy(r2p).cuda(), k=1)
+    torch.cuda.synchronize()
+    rows = host_bf16(x[-500:].contiguous())[r2p - (T - 500)]
+    ref = oracle.grouped_ffn(rows, offs, w13, w2)
+    assert_close_rel(bf16_f64(host_bf16(y)), ref, what="x above 4 GiB")
