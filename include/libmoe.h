@@ -216,15 +216,16 @@ moe_status moe_combine(const uint16_t *y, int64_t y_rows, const int32_t *pair_to
  *   (or moe_grouped_ffn without a shared expert; the row gather fused) ->
  *   moe_combine (accumulate = 0, the shared rows added)
  * with every intermediate written to the caller's buffers, bit for bit what
- * those four calls write.  Where the shapes allow it (at most 64 local
- * experts, the large-tile FFN shapes: H and I_s multiples of 64, at least
- * 128), routing, the permutation and the FFN's tile schedule run in fused
- * launches: for small inputs (pairs x (bits of the local expert index + 2)
- * at most 16384, e.g. 2048 pairs over 32 experts) routing, then the
- * permutation with the schedule in one workgroup; for larger ones routing
- * with the permutation's histogram, then its scan and scatter with the
- * schedule: two launches instead of three or four.  Otherwise it runs the
- * four calls' launches.
+ * those four calls write.  Batches of few rows per expert (decode) take no
+ * FFN tile schedule: routing, the permutation, two streaming GEMMs, the
+ * combine.  Otherwise, where the shapes allow it (at most 64 local experts, H
+ * and I_s multiples of 64, at least 128), routing, the permutation and the
+ * FFN's tile schedule run in fused launches: for small inputs (pairs x (bits
+ * of the local expert index + 2) at most 16384, e.g. 2048 pairs over 32
+ * experts) routing, then the permutation with the schedule in one workgroup;
+ * for larger ones routing with the permutation's histogram, then its scan and
+ * scatter with the schedule: two launches instead of three or four.  Other
+ * shapes run the four calls' launches.
  *   x [T, H] bf16; logits [T, E] fp32; w13, w2 and shared_w13 [2*I_s, H],
  *   shared_w2 [H, I_s] as for moe_grouped_ffn(_shared) (the shared expert,
  *   on token rows [shared_begin, shared_begin + shared_count), has the
@@ -397,8 +398,9 @@ typedef enum moe_kernel_kind {
     MOE_K_SPLITK_REDUCE = 7, /* combination of split-K partials of the large tiles (long K only) */
     MOE_K_RESHARD = 8,       /* expert-weight resharding */
     MOE_K_KV_MOVE = 9,       /* paged KV head moves (and their slot expansion) */
-    MOE_K_LAYER_PREP = 10,   /* moe_layer_forward: the fused launches of permutation and tile schedule
-                                (with routing on larger inputs; on small ones routing is timed as MOE_K_ROUTE) */
+    MOE_K_LAYER_PREP = 10,   /* moe_layer_forward: the launches that prepare the FFN: the permutation (decode), or
+                                the fused permutation and tile schedule (with routing on larger inputs; on smaller
+                                ones routing is timed as MOE_K_ROUTE) */
     MOE_K_COUNT = 11
 } moe_kernel_kind;
 

@@ -14,6 +14,8 @@
 #include <type_traits>
 #include <vector>
 
+#include "ffn_dev.h"
+#include "ffn_stream.h"
 #include "moe_internal.h"
 #include "permute_dev.h"
 #include "route_dev.h"
@@ -21,28 +23,10 @@
 namespace moe {
 namespace {
 
+using namespace ffn_dev;
+
 constexpr int BM = 64, BN = 64, BK = 64;  // the general kernel (operands past 32-bit byte offsets)
 constexpr int KCH = BK / 8;               // 16-byte chunks per tile row
-
-__device__ __forceinline__ int64_t clamp_row(int32_t v, int64_t cap)
-{
-    int64_t r = v < 0 ? 0 : v;
-    return r > cap ? cap : r;
-}
-
-// Row range of expert e in one call's row space: a routed expert e < El holds
-// [offsets[e], offsets[e+1]) clamped to [0, cap]; the shared expert (e == El,
-// present when the call has shared rows) holds [cap, cap + shared_rows).
-__device__ __forceinline__ int64_t expert_begin(const int32_t *__restrict__ offsets, int El, int64_t cap, int e)
-{
-    return e < El ? clamp_row(offsets[e], cap) : cap;
-}
-
-__device__ __forceinline__ int64_t expert_end(const int32_t *__restrict__ offsets, int El, int64_t cap,
-                                              int64_t shared_rows, int e)
-{
-    return e < El ? clamp_row(offsets[e + 1], cap) : cap + shared_rows;
-}
 
 // A read of metadata that earlier launches wrote and the grouped GEMM only
 // reads (the schedule's tile lists and cuts, the experts' row offsets),
@@ -54,13 +38,6 @@ template <class T>
 __device__ __forceinline__ T ld_meta(const T *p)
 {
     return *(const __attribute__((address_space(4))) T *)p;
-}
-
-// SwiGLU of one gate/up pair: silu(g) * u = g / (1 + e^-g) * u, with the
-// hardware reciprocal (the result is rounded to bf16).
-__device__ __forceinline__ float silu_mul(float g, float u)
-{
-    return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
 
 // Large-tile launches split K only from this many K-slices per tile.
@@ -802,12 +779,6 @@ __device__ __forceinline__ void mfma_step_own(f32x16_t (&acc)[MB][NB], const Fra
             }
         }
     }
-}
-
-__device__ __forceinline__ uint16_t bf16_bits(float f)
-{
-    __bf16 h = static_cast<__bf16>(f);  // round to nearest even
-    return *reinterpret_cast<uint16_t *>(&h);
 }
 
 // Coordinates of tile `tile` of a tile class: expert e, rows [r0, r1) and
@@ -1598,7 +1569,7 @@ __device__ __forceinline__ SmallGroup small_group(int64_t tl, int64_t ts, int nk
 constexpr int DEV_TS_SLOTS = 4096;
 __device__ unsigned long long g_dev_ts[2][8][DEV_TS_SLOTS];  // [0]: start (min), [1]: end (max), per die
 
-// One grouped GEMM launch: the large-tile class (256-row tiles) and the
+// One grouped GEMM launch of a call that the streaming kernels do not serve: the large-tile class (256-row tiles) and the
 // small-row class (64- or 128-row tiles as the schedule chose, K-split over
 // its workgroups: these stream weights, and spreading them over many CUs is
 // what reaches HBM bandwidth) in the same persistent grid.  The classes
@@ -2004,6 +1975,112 @@ struct FfnCall {
     int bm() const { return big ? BIGM : BM; }
 };
 
+// Whether the streaming kernels (ffn_stream.h) serve a call: they read every
+// active expert's weights once per 64 rows, so they are for few rows per
+// expert.  What the host knows is a bound on any expert's rows (the tokens
+// of a gathered call, where no expert takes a token twice; else all rows) and
+// a bound on the mean, R = cap / El (an EP rank's own mean is lower).  The
+// lines lie where the streaming kernels stop being faster whatever the load
+// (us, tiled / streaming):
+//   at most 64 rows: one expert with all 64 rows of H 4096, I 14336 117 / 120,
+//     32 rows 109 / 90; 32 + 1 experts of H 7168, I 2048, 64 tokens 398 / 370;
+//   up to 128 tokens, mean at most 64: 16 experts of H 4096, I 1536 141 / 111
+//     (one expert with most of 96 tokens: 154 / 190);
+//   up to 512 tokens, mean at most 32: 128 slices of H 4096, I 192, 512 tokens
+//     174 / 154 (1024 tokens, mean 64: 262 / 258);
+//   without a gather, up to 512 rows, mean at most 16: 16 experts of H 4096,
+//     I 1536 under a Zipf load, 256 rows 138 / 131 (512 rows: 142 / 178);
+//   weights of a few MB, which stay in the caches: mean at most 128 (8
+//     experts of H 256, I 512, 512 tokens 56 / 36; 1024 tokens 56 / 53).
+constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20;
+bool stream_call(const FfnCall &c, int64_t x_rows, bool gather)
+{
+    if (!c.big || c.H > (1 << 20) || c.Is > (1 << 20)) return false;
+    const int64_t rows = gather ? x_rows : c.rows, R = ceil_div(c.cap, c.El);
+    if (rows <= 64) return true;
+    if ((int64_t)c.El * 6 * c.H * c.Is <= STREAM_CACHED_BYTES && rows <= 512) return true;
+    if (gather) return (rows <= 128 && R <= 64) || (rows <= 512 && R <= 32);
+    return rows <= 512 && R <= 16;
+}
+
+template <bool GATED>
+hipError_t launch_stream(ffn_stream::StreamArgs a, int64_t rows, int ne, int kind, hipStream_t s)
+{
+    ffn_stream::LaunchStamps ts{nullptr, nullptr, DEV_TS_SLOTS};
+    const int slot = device_ts_slot(kind);
+    if (slot >= 0) {
+        void *p = nullptr;
+        const hipError_t err = hipGetSymbolAddress(&p, HIP_SYMBOL(g_dev_ts));
+        if (err != hipSuccess) return err;
+        ts.start = static_cast<unsigned long long *>(p) + slot;
+        ts.end = ts.start + 8 * DEV_TS_SLOTS;
+    }
+    // Waves that split K (2^lks of them): as many as leave each at least three
+    // slices, up to four (eight never helped: the 64-token DeepSeek-shaped
+    // slice 370 us with four, 398 with eight, 415 with one), or two slices
+    // where the launch would not give every SIMD a wave (the tiny replicated
+    // layer 21.8 -> 20.5 us).  K decides, and the bounds that a layer call and
+    // its four separate calls both know, so both sum in the same order.
+    const int64_t active = ne < a.cap + a.shared_rows ? ne : a.cap + a.shared_rows, R = ceil_div(a.cap, a.El);
+    const int slices = a.K / ffn_stream::SK;
+    auto waves = [&](int nb, int lks) { return active * ceil_div(a.N, GATED ? 8 * nb : 16 * nb) << lks; };
+    a.lks = 0;
+    while (a.lks < 2 && (slices >> (a.lks + 1)) >= 3) ++a.lks;
+    if (a.lks < 2 && waves(2, a.lks) < 1024 && (slices >> (a.lks + 1)) >= 2) ++a.lks;
+    // Row blocks per pass of an expert: what its rows can fill, but two where
+    // the mean is low (more waves fit beside each other: 128 slices of 64
+    // tokens 118 -> 111 us).  Four row blocks read as many activations as
+    // weights, so they take strips of four weight blocks where that leaves
+    // enough waves (8 experts of H 4096, I 7168, 96 tokens: 277 -> 237 us; one
+    // expert's down projection of 128 strips stays at two blocks: 125 -> 106).
+    const int mb = rows <= 16 ? 1 : rows <= 32 || R <= 12 ? 2 : 4;
+    const int nb = mb == 4 && waves(4, a.lks) >= 1024 ? 4 : 2;
+    const int nw = a.lks == 2 ? 4 : 2, per = nw >> a.lks;
+    const dim3 grid((unsigned)ceil_div(ceil_div(a.N, GATED ? 8 * nb : 16 * nb), per), (unsigned)ne);
+    const size_t lds = (size_t)nw * (mb + nb) * 2048;
+    // Weights that cannot stay in the caches are loaded with the non-temporal
+    // hint (64 tokens of the DeepSeek-shaped slice 420 -> 373 us), where the
+    // rows are whole 128-byte lines: rows of 192 bytes share lines with their
+    // neighbours (I_s = 96: 59 -> 61 us with the hint).
+    const bool nt = a.K % ffn_stream::SK == 0 && active * a.N * (GATED ? 2 : 1) * a.K * 2 > ((int64_t)64 << 20);
+#define GO(NT, MB, NB, W) ffn_stream::stream_kernel<GATED, NT, MB, NB, W><<<grid, dim3(64 * nw), lds, s>>>(a, ts)
+#define GO_NT(MB, NB, W)          \
+    do {                          \
+        if (nt)                   \
+            GO(true, MB, NB, W);  \
+        else                      \
+            GO(false, MB, NB, W); \
+    } while (0)
+    if (mb == 1) GO_NT(1, 2, 4);
+    else if (mb == 2) GO_NT(2, 2, 3);
+    else if (nb == 2) GO_NT(4, 2, 2);
+    else GO_NT(4, 4, 2);
+#undef GO_NT
+#undef GO
+    return hipGetLastError();
+}
+
+// Both GEMMs of a call that the streaming kernels serve.
+hipError_t launch_stream_gemms(const FfnCall &c, const uint16_t *x, int64_t x_rows, const int32_t *row_index, int kdiv,
+                               const int32_t *offsets, const uint16_t *w13, const uint16_t *w2, uint16_t *y,
+                               int64_t shared_begin, const uint16_t *sw13, const uint16_t *sw2, uint16_t *shared_y,
+                               hipStream_t s)
+{
+    const int El = c.El, H = c.H, Is = c.Is, cap = (int)c.cap, sc = (int)c.sc;
+    const int64_t rows = row_index ? x_rows : c.rows;
+    hipError_t err;
+    {
+        KernelTimer timer(MOE_K_GATE_UP, s);
+        const ffn_stream::StreamArgs a{x, row_index, kdiv, row_index ? x_rows : c.rows, offsets, El, cap, sc, (int)shared_begin, Is, H,
+                                       w13, (int64_t)2 * Is * H, sw13, Is, c.h, c.h_sh, 0};
+        if ((err = launch_stream<true>(a, rows, c.ne, MOE_K_GATE_UP, s)) != hipSuccess) return err;
+    }
+    KernelTimer timer(MOE_K_DOWN, s);
+    const ffn_stream::StreamArgs a{c.h, nullptr, 1, c.rows, offsets, El, cap, sc, (int)shared_begin, H, Is,
+                                   w2, (int64_t)H * Is, sw2, 0, y, shared_y, 0};
+    return launch_stream<false>(a, rows, c.ne, MOE_K_DOWN, s);
+}
+
 // The GEMM launches of a call whose schedule is already in the workspace.
 hipError_t launch_gemms(const FfnCall &c, const uint16_t *x, int64_t x_rows, const int32_t *row_index, int kdiv,
                         const int32_t *offsets, const uint16_t *w13, const uint16_t *w2, uint16_t *y,
@@ -2089,6 +2166,9 @@ hipError_t launch_grouped_ffn(const uint16_t *x, int64_t x_rows, const int32_t *
     if (cap + shared_rows == 0) return hipSuccess;
     const FfnCall c(x_rows, row_index != nullptr, El, cap, H, Is, shared_rows, ws);
     if (shared_rows > 0 && !c.big) return hipErrorNotSupported;  // the host API checks this first
+    if (stream_call(c, x_rows, row_index != nullptr))
+        return launch_stream_gemms(c, x, x_rows, row_index, kdiv, offsets, w13, w2, y, shared_begin, sw13, sw2,
+                                   shared_y, s);
     {
         KernelTimer timer(MOE_K_SCHEDULE, s);
         const unsigned threads = (unsigned)(ceil_div(c.ne > 256 ? c.ne : 256, 64) * 64);
@@ -2167,6 +2247,17 @@ hipError_t launch_layer(const uint16_t *x, const float *logits, int64_t T, int E
         return launch_combine(y, cap, p2r, w, T, k, H, sc > 0 ? shared_y : nullptr, sb, sc, 0, out, s);
     }
     const FfnCall c(T, true, El, cap, H, Is, sc, ws_ffn);
+    if (stream_call(c, T, true)) {
+        // the streaming GEMMs take no tile schedule: the permutation is all
+        // the preparation
+        if ((err = launch_route(logits, T, E, k, ids, w, s)) != hipSuccess) return err;
+        if ((err = launch_permute(ids, T, k, e0, El, counts, offsets, r2p, p2r, nullptr, 0, nullptr, cap, ws_perm, s,
+                                  MOE_K_LAYER_PREP)) != hipSuccess)
+            return err;
+        if ((err = launch_stream_gemms(c, x, T, r2p, k, offsets, w13, w2, y, sb, sw13, sw2, shared_y, s)) != hipSuccess)
+            return err;
+        return launch_combine(y, cap, p2r, w, T, k, H, sc > 0 ? shared_y : nullptr, sb, sc, 0, out, s);
+    }
     int nbits = 0;
     while ((1 << nbits) < El + 2) ++nbits;
     const bool small = npairs <= permute_dev::SMALL_PAIRS && npairs * (nbits + 2) <= LAYER_SMALL_WORK;

@@ -312,7 +312,7 @@ int64_t permute_chunks(int64_t T, int k, int El) { return ceil_div(T * k, chunk_
 hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, int32_t *counts,
                           int32_t *offsets, int32_t *row_to_pair, int32_t *pair_to_row,
                           const uint16_t *x, int H, uint16_t *x_perm, int64_t cap, int32_t *ws,
-                          hipStream_t s)
+                          hipStream_t s, int kind)
 {
     const int64_t npairs = T * k;
     const int64_t nchunks = permute_chunks(T, k, El);
@@ -321,12 +321,12 @@ hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, 
     while ((1 << nbits) < El + 2) ++nbits;  // distinguishes 0..El+1
     hipError_t err;
     if (npairs > 0 && npairs <= SMALL_PAIRS && El <= 64 && npairs * (nbits + 2) <= SMALL_WORK) {
-        KernelTimer timer(MOE_K_PERMUTE, s);
+        KernelTimer timer(kind, s);
         permute_small_kernel<<<dim3(1), dim3(1024), 0, s>>>(ids, npairs, e0, El, nbits, counts, offsets,
                                                              row_to_pair, pair_to_row);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     } else {
-        KernelTimer timer(MOE_K_PERMUTE, s);
+        KernelTimer timer(kind, s);
         if (nchunks > 0) {
             if (short_chunks)
                 count_kernel<4><<<dim3((unsigned)nchunks), dim3(64), El * sizeof(int32_t), s>>>(

@@ -1,0 +1,82 @@
+"""The streaming expert FFN (few rows per expert; needs an MI355X) at the
+edges of its row blocks, weight strips and K splits, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import moe_inputs as mi
+import paper_2606_26607_amd as moe
+from tests.util import assert_close_rel, bf16_f64, dev_bf16, host_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    moe.lib()
+
+
+# rows per expert; at most 64 rows in all, or (with gathered rows of at most 64 tokens) experts of more
+ONE = [1]
+B16 = [16, 0, 15, 17, 1]
+B64 = [64]
+B33 = [33, 31]
+MORE = [65, 130, 0, 20, 48]    # passes of 64, 32 and 16 rows, at different points in different waves
+
+
+@pytest.mark.parametrize("rows,gather,H,Is", [
+    (ONE, False, 8, 8),             # one chunk of one slice
+    (ONE, True, 4096, 2048),        # K split four ways
+    (B16, False, 64, 24),           # one whole slice; a strip past the columns
+    (B16, True, 136, 200),          # partial slices, one strip of columns short
+    (B16, False, 256, 512),         # K split two ways
+    (B64, False, 1000, 328), (B64, False, 2056, 40),
+    (B33, True, 768, 1536), (B33, False, 72, 1032),
+    (MORE, True, 256, 512), (MORE, True, 200, 120), (MORE, True, 1024, 4096),
+])
+def test_stream_edges(oracle, rows, gather, H, Is):
+    El, k, n = len(rows), 3, sum(rows)
+    offs = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    T = 64 if gather else n
+    x = mi.random_bf16((T, H), seed=H + Is, tag=80)
+    w13 = mi.random_bf16((El, 2 * Is, H), seed=H, tag=81, std=0.05)
+    w2 = mi.random_bf16((El, H, Is), seed=H, tag=82, std=0.05)
+    r2p = np.random.default_rng(H + n).integers(0, T * k, n).astype(np.int32) if gather else None
+    want = oracle.grouped_ffn(x if r2p is None else x[r2p // k], offs, w13, w2)
+    runs = []
+    for _ in range(2):
+        y = torch.full((n + 1, H), 7.0, dtype=torch.bfloat16, device="cuda")
+        moe.grouped_ffn(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), y=y, cap_rows=n,
+                        row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1)
+        torch.cuda.synchronize()
+        runs.append(host_bf16(y))
+    np.testing.assert_array_equal(runs[0], runs[1])
+    assert np.all(bf16_f64(runs[0])[n] == 7.0)  # nothing past the rows
+    assert_close_rel(bf16_f64(runs[0])[:n], want, what=f"rows={rows} H={H} Is={Is}")
+
+
+@pytest.mark.parametrize("T", [5, 40, 128])
+def test_stream_shared_and_non_temporal(oracle, T):
+    """Weights of more than 64 MiB (loaded with the non-temporal hint), a shared expert beside the routed ones, and
+    every row-block width."""
+    El, E, k, H, Is = 8, 16, 4, 2048, 1088
+    ids = mi.random_topk_ids(T, E, k, seed=T)
+    _, offs, r2p, _ = oracle.permute(ids, 4, El)
+    n, sb, sc = int(offs[-1]), T // 3, T // 2
+    x = mi.random_bf16((T, H), seed=T, tag=83)
+    w13 = mi.random_bf16((El, 2 * Is, H), seed=1, tag=84, std=0.03)
+    w2 = mi.random_bf16((El, H, Is), seed=1, tag=85, std=0.03)
+    sw13 = mi.random_bf16((2 * Is, H), seed=1, tag=86, std=0.03)
+    sw2 = mi.random_bf16((H, Is), seed=1, tag=87, std=0.03)
+    cap = T * k
+    full = torch.full((cap,), -1, dtype=torch.int32)
+    full[:n] = torch.from_numpy(r2p)
+    y, sy = moe.grouped_ffn_shared(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2),
+                                   full.cuda(), k, cap, sb, sc, dev_bf16(sw13), dev_bf16(sw2))
+    torch.cuda.synchronize()
+    assert_close_rel(bf16_f64(host_bf16(y))[:n], oracle.grouped_ffn(x[r2p // k], offs, w13, w2), what="routed")
+    assert_close_rel(bf16_f64(host_bf16(sy))[:sc],
+                     oracle.grouped_ffn(x[sb:sb + sc], np.array([0, sc], np.int32), sw13[None], sw2[None]),
+                     what="shared")
