@@ -225,7 +225,8 @@ moe_status moe_combine(const uint16_t *y, int64_t y_rows, const int32_t *pair_to
  * experts) routing, then the permutation with the schedule in one workgroup;
  * for larger ones routing with the permutation's histogram, then its scan and
  * scatter with the schedule: two launches instead of three or four.  Other
- * shapes run the four calls' launches.
+ * shapes run the same steps in launches of their own (routing with the
+ * permutation's histogram for up to 256 local experts).
  *   x [T, H] bf16; logits [T, E] fp32; w13, w2 and shared_w13 [2*I_s, H],
  *   shared_w2 [H, I_s] as for moe_grouped_ffn(_shared) (the shared expert,
  *   on token rows [shared_begin, shared_begin + shared_count), has the

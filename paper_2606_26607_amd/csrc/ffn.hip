@@ -1706,12 +1706,35 @@ __global__ __launch_bounds__(1024) void layer_perm_sched_kernel(const int32_t *_
                                                                 int64_t sc, SchedShape sh, SchedOut so,
                                                                 int32_t *__restrict__ counters, int64_t n_counters)
 {
-    permute_dev::permute_small_body(ids, npairs, e0, El, nbits, counts, offsets, row_to_pair, pair_to_row);
+    permute_dev::permute_small_body<64>(ids, npairs, e0, El, nbits, counts, offsets, row_to_pair, pair_to_row);
     __syncthreads();  // the offsets are visible to the block
     schedule_body<LAYER_NE_MAX>(offsets, El, cap, sc, BIGM, true, sh, so, counters, n_counters);
 }
 
-// Larger inputs, at most 64 local experts: block c routes the tokens that
+// Few tokens over few experts: routing and the permutation in one workgroup
+// of 1024 threads (the whole preparation of a streaming FFN).  The ids go
+// through LDS; route_in_one_workgroup says where this pays.
+constexpr int RP_PAIRS = 1024;
+template <int G, int S, int EM>
+__global__ __launch_bounds__(1024) void layer_route_perm_kernel(const float *__restrict__ logits, int64_t T, int E,
+                                                               int k, int e0, int El, int nbits,
+                                                               int32_t *__restrict__ ids, float *__restrict__ w,
+                                                               int32_t *__restrict__ counts,
+                                                               int32_t *__restrict__ offsets,
+                                                               int32_t *__restrict__ row_to_pair,
+                                                               int32_t *__restrict__ pair_to_row)
+{
+    __shared__ int32_t lid[RP_PAIRS];
+    const int tid = threadIdx.x, sub = tid % G;
+    for (int64_t t = tid / G; t < T; t += 1024 / G)
+        route_dev::route_token<G, S>(logits + t * E, E, k, sub, lid + t * k, w + t * k);
+    __syncthreads();
+    const int64_t npairs = T * k;
+    for (int64_t p = tid; p < npairs; p += 1024) ids[p] = lid[p];
+    permute_dev::permute_small_body<EM>(lid, npairs, e0, El, nbits, counts, offsets, row_to_pair, pair_to_row);
+}
+
+// Larger inputs, at most 256 local experts: block c routes the tokens that
 // have a pair in chunk c of the pairs (CH = ROUNDS * 64 pairs, the
 // permutation's chunks), writes those whose first pair lies in the chunk
 // (every token once over the grid) and counts the chunk's pairs per local
@@ -1726,7 +1749,7 @@ __global__ __launch_bounds__(RC_THREADS) void layer_route_count_kernel(const flo
     constexpr int CH = ROUNDS * 64;
     __shared__ int32_t lid[CH + 2 * MOE_MAX_TOPK];
     __shared__ float lw[CH + 2 * MOE_MAX_TOPK];
-    __shared__ int32_t hist[64];
+    __shared__ int32_t hist[permute_dev::WIDE_EXPERTS];
     const int tid = threadIdx.x;
     const int64_t npairs = T * k, p0 = (int64_t)blockIdx.x * CH;
     const int64_t p1 = p0 + CH < npairs ? p0 + CH : npairs;
@@ -1734,7 +1757,7 @@ __global__ __launch_bounds__(RC_THREADS) void layer_route_count_kernel(const flo
     const int sub = tid % G;
     for (int64_t t = ta + tid / G; t < tb; t += RC_THREADS / G)
         route_dev::route_token<G, S>(logits + t * E, E, k, sub, lid + (t - ta) * k, lw + (t - ta) * k);
-    if (tid < 64) hist[tid] = 0;
+    if (tid < permute_dev::WIDE_EXPERTS) hist[tid] = 0;
     __syncthreads();
     const int64_t tw = (p0 + k - 1) / k;  // the first token whose first pair lies in the chunk
     for (int64_t q = tw * k + tid; q < tb * k; q += RC_THREADS) {
@@ -1765,7 +1788,7 @@ __global__ __launch_bounds__(256) void layer_scan_sched_kernel(const int32_t *__
 {
     const int64_t nb = (nchunks + 3) / 4;
     if ((int64_t)blockIdx.x < nb) {
-        permute_dev::scan_scatter_body<ROUNDS>(ids, npairs, e0, El, nbits, chunk_cnt, nchunks, counts, offsets,
+        permute_dev::scan_scatter_body<ROUNDS, 64>(ids, npairs, e0, El, nbits, chunk_cnt, nchunks, counts, offsets,
                                                row_to_pair, pair_to_row, blockIdx.x);
         return;
     }
@@ -2214,13 +2237,82 @@ struct LaunchRouteCount {
     }
 };
 
+// Whether routing and permutation run in one workgroup: a launch costs about
+// 4.2 us, and the routing then runs on one CU, whose time grows with the
+// rounds of the top-k (k), the logits a lane holds (S) and the waves that
+// share a SIMD.  About 5000 cycles of it still gain (the tiny replicated
+// layer, 64 tokens over 8 experts, needs 1200 and gains; 64 tokens
+// over 256 experts need 21000).
+bool route_in_one_workgroup(int64_t T, int E, int k, int El)
+{
+    if (E > 256 || T * k > RP_PAIRS || !permute_one_workgroup(T * k, El)) return false;
+    const int G = E <= 8 ? 8 : E <= 16 || T > 16 ? 16 : 64;
+    const int64_t cycles = 4 * (int64_t)k * (6 * ceil_div(E, G) + 70) * ceil_div(T * G, 256);
+    return cycles <= 5000;
+}
+
+hipError_t launch_route_perm(const float *logits, int64_t T, int E, int k, int e0, int El, int32_t *ids, float *w,
+                             int32_t *counts, int32_t *offsets, int32_t *r2p, int32_t *p2r, hipStream_t s)
+{
+    const int nbits = permute_bits(El);
+#define GO(G, S, EM)                                                                                     \
+    layer_route_perm_kernel<G, S, EM><<<dim3(1), dim3(1024), 0, s>>>(logits, T, E, k, e0, El, nbits, ids, w, counts, \
+                                                                     offsets, r2p, p2r)
+#define GO_EM(G, S)                              \
+    do {                                         \
+        if (El <= 64)                            \
+            GO(G, S, 64);                        \
+        else                                     \
+            GO(G, S, permute_dev::WIDE_EXPERTS); \
+    } while (0)
+    if (E <= 8) GO(8, 1, 64);
+    else if (E <= 16) GO(16, 1, 64);
+    else if (T <= 16 && E <= 64) GO(64, 1, 64);
+    else if (T <= 16 && E <= 128) GO_EM(64, 2);
+    else if (T <= 16) GO_EM(64, 4);
+    else if (E <= 32) GO(16, 2, 64);
+    else if (E <= 64) GO(16, 4, 64);
+    else if (E <= 128) GO_EM(16, 8);
+    else GO_EM(16, 16);
+#undef GO_EM
+#undef GO
+    return hipGetLastError();
+}
+
+// Routing and permutation of a layer whose FFN takes its schedule from a
+// launch of its own, or none: in one workgroup, or the routing with the
+// permutation's histogram and then its scan and scatter, or the launches of
+// the separate calls.
+hipError_t launch_route_permute(const float *logits, int64_t T, int E, int k, int e0, int El, int32_t *ids, float *w,
+                                int32_t *counts, int32_t *offsets, int32_t *r2p, int32_t *p2r, int64_t cap,
+                                int32_t *ws_perm, int kind, hipStream_t s)
+{
+    hipError_t err;
+    if (route_in_one_workgroup(T, E, k, El)) {
+        KernelTimer timer(kind, s);
+        return launch_route_perm(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, s);
+    }
+    const int64_t nchunks = permute_chunks(T, k, El);
+    if (!permute_one_workgroup(T * k, El) && permute_dev::scan_scatter_serves(nchunks, El)) {
+        {
+            KernelTimer timer(MOE_K_ROUTE, s);
+            err = by_experts<LaunchRouteCount>(E, logits, T, E, k, e0, El, ids, w, ws_perm, nchunks,
+                                               permute_dev::chunk_pairs(T * k, El) == 256, s);
+            if (err != hipSuccess) return err;
+        }
+        KernelTimer timer(kind, s);
+        return launch_scan_scatter(ids, T, k, e0, El, counts, offsets, r2p, p2r, ws_perm, s);
+    }
+    if ((err = launch_route(logits, T, E, k, ids, w, s)) != hipSuccess) return err;
+    return launch_permute(ids, T, k, e0, El, counts, offsets, r2p, p2r, nullptr, 0, nullptr, cap, ws_perm, s, kind);
+}
+
 }  // namespace
 
 bool layer_fused_prep(int64_t T, int k, int El, int H, int Is, int64_t sc)
 {
     const int64_t npairs = T * k, cap = T * (k < El ? k : El);
-    int nbits = 0;
-    while ((1 << nbits) < El + 2) ++nbits;
+    const int nbits = permute_bits(El);
     const bool fuse = npairs > 0 && El <= 64 && El + (sc > 0 ? 1 : 0) <= LAYER_NE_MAX && ffn_whole_slices(H, Is) &&
                       ffn_large_tiles(T, cap + sc, H, Is);
     const bool small = npairs <= permute_dev::SMALL_PAIRS && npairs * (nbits + 2) <= LAYER_SMALL_WORK;
@@ -2236,10 +2328,9 @@ hipError_t launch_layer(const uint16_t *x, const float *logits, int64_t T, int E
     const int64_t npairs = T * k, cap = T * (k < El ? k : El);
     hipError_t err;
     if (!layer_fused_prep(T, k, El, H, Is, sc)) {
-        // the separate launches of the four calls
-        if ((err = launch_route(logits, T, E, k, ids, w, s)) != hipSuccess) return err;
-        if ((err = launch_permute(ids, T, k, e0, El, counts, offsets, r2p, p2r, nullptr, 0, nullptr, cap, ws_perm,
-                                  s)) != hipSuccess)
+        // (the streaming GEMMs take no schedule, so this serves them too)
+        if ((err = launch_route_permute(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, cap, ws_perm,
+                                        MOE_K_PERMUTE, s)) != hipSuccess)
             return err;
         if ((err = launch_grouped_ffn(x, T, r2p, k, offsets, El, cap, H, Is, w13, w2, y, sb, sc, sw13, sw2,
                                       shared_y, ws_ffn, s)) != hipSuccess)
@@ -2250,16 +2341,14 @@ hipError_t launch_layer(const uint16_t *x, const float *logits, int64_t T, int E
     if (stream_call(c, T, true)) {
         // the streaming GEMMs take no tile schedule: the permutation is all
         // the preparation
-        if ((err = launch_route(logits, T, E, k, ids, w, s)) != hipSuccess) return err;
-        if ((err = launch_permute(ids, T, k, e0, El, counts, offsets, r2p, p2r, nullptr, 0, nullptr, cap, ws_perm, s,
-                                  MOE_K_LAYER_PREP)) != hipSuccess)
+        if ((err = launch_route_permute(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, cap, ws_perm,
+                                        MOE_K_LAYER_PREP, s)) != hipSuccess)
             return err;
         if ((err = launch_stream_gemms(c, x, T, r2p, k, offsets, w13, w2, y, sb, sw13, sw2, shared_y, s)) != hipSuccess)
             return err;
         return launch_combine(y, cap, p2r, w, T, k, H, sc > 0 ? shared_y : nullptr, sb, sc, 0, out, s);
     }
-    int nbits = 0;
-    while ((1 << nbits) < El + 2) ++nbits;
+    const int nbits = permute_bits(El);
     const bool small = npairs <= permute_dev::SMALL_PAIRS && npairs * (nbits + 2) <= LAYER_SMALL_WORK;
     if (small && (err = launch_route(logits, T, E, k, ids, w, s)) != hipSuccess) return err;
     {

@@ -53,6 +53,21 @@ hipError_t launch_route(const float *logits, int64_t T, int E, int k, int32_t *i
                         hipStream_t s);
 
 int64_t permute_chunks(int64_t T, int k, int El);
+// Bits that tell local expert indices 0 .. El + 1 apart (El and El + 1 mark
+// pairs owned elsewhere and lanes without a pair).
+inline int permute_bits(int El)
+{
+    int nbits = 0;
+    while ((1 << nbits) < El + 2) ++nbits;
+    return nbits;
+}
+// Whether the permutation of npairs pairs runs in one workgroup.
+bool permute_one_workgroup(int64_t npairs, int El);
+// The permutation's scan and scatter in one launch, after the chunks' counts
+// (permute_dev::scan_scatter_serves says where).
+hipError_t launch_scan_scatter(const int32_t *ids, int64_t T, int k, int e0, int El, int32_t *counts,
+                               int32_t *offsets, int32_t *row_to_pair, int32_t *pair_to_row,
+                               const int32_t *chunk_cnt, hipStream_t s);
 // Device address of the current device's permutation scratch array
 // (MOE_PERMUTE_SCRATCH_BYTES), looked up once per device.
 hipError_t permute_scratch(int32_t **ptr);

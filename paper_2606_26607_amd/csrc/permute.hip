@@ -14,9 +14,9 @@
 //               among equal lanes.  No global atomics: the result is the
 //               unique stable order, identical on every run.
 //   4. gather:  optional copy of x rows into permuted order (16-byte moves).
-// Small inputs (decode: at most 16384 pairs over at most 64 local experts,
+// Small inputs (decode: at most 16384 pairs over at most 256 local experts,
 // and a bounded amount of ballot work, see SMALL_WORK) run steps 1-3 in one
-// workgroup instead, saving launches; larger ones with at most 64 local
+// workgroup instead, saving launches; larger ones with at most 256 local
 // experts run steps 2 and 3 in one launch.
 #include <mutex>
 
@@ -191,6 +191,7 @@ __global__ __launch_bounds__(1024) void scan_narrow_kernel(int32_t *__restrict__
     }
 }
 
+template <int EM>
 __global__ __launch_bounds__(1024) void permute_small_kernel(const int32_t *__restrict__ ids, int64_t npairs,
                                                              int e0, int El, int nbits,
                                                              int32_t *__restrict__ counts,
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(1024) void permute_small_kernel(const int32_t *__re
                                                              int32_t *__restrict__ row_to_pair,
                                                              int32_t *__restrict__ pair_to_row)
 {
-    permute_small_body(ids, npairs, e0, El, nbits, counts, offsets, row_to_pair, pair_to_row);
+    permute_small_body<EM>(ids, npairs, e0, El, nbits, counts, offsets, row_to_pair, pair_to_row);
 }
 
 template <int ROUNDS>
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(64) void scatter_kernel(const int32_t *__restrict__
     }
 }
 
-template <int ROUNDS>
+template <int ROUNDS, int EM>
 __global__ __launch_bounds__(256) void scan_scatter_kernel(const int32_t *__restrict__ ids, int64_t npairs,
                                                           int e0, int El, int nbits,
                                                           const int32_t *__restrict__ chunk_cnt, int64_t nchunks,
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(256) void scan_scatter_kernel(const int32_t *__rest
                                                           int32_t *__restrict__ row_to_pair,
                                                           int32_t *__restrict__ pair_to_row)
 {
-    scan_scatter_body<ROUNDS>(ids, npairs, e0, El, nbits, chunk_cnt, nchunks, counts, offsets, row_to_pair,
+    scan_scatter_body<ROUNDS, EM>(ids, npairs, e0, El, nbits, chunk_cnt, nchunks, counts, offsets, row_to_pair,
                               pair_to_row, blockIdx.x);
 }
 
@@ -309,6 +310,36 @@ hipError_t permute_scratch(int32_t **ptr)
 
 int64_t permute_chunks(int64_t T, int k, int El) { return ceil_div(T * k, chunk_pairs(T * k, El)); }
 
+bool permute_one_workgroup(int64_t npairs, int El)
+{
+    return npairs > 0 && npairs <= SMALL_PAIRS && El <= WIDE_EXPERTS && npairs * (permute_bits(El) + 2) <= SMALL_WORK;
+}
+
+hipError_t launch_scan_scatter(const int32_t *ids, int64_t T, int k, int e0, int El, int32_t *counts,
+                               int32_t *offsets, int32_t *row_to_pair, int32_t *pair_to_row,
+                               const int32_t *chunk_cnt, hipStream_t s)
+{
+    const int64_t npairs = T * k, nchunks = permute_chunks(T, k, El);
+    const int nbits = permute_bits(El);
+    const unsigned blocks = (unsigned)ceil_div(nchunks, 4);
+#define GO(ROUNDS, EM)                                                                                            \
+    scan_scatter_kernel<ROUNDS, EM><<<dim3(blocks), dim3(256), 0, s>>>(ids, npairs, e0, El, nbits, chunk_cnt, nchunks, \
+                                                                       counts, offsets, row_to_pair, pair_to_row)
+    if (chunk_pairs(npairs, El) == 256) {
+        if (El <= 64)
+            GO(4, 64);
+        else
+            GO(4, WIDE_EXPERTS);
+    } else {
+        if (El <= 64)
+            GO(16, 64);
+        else
+            GO(16, WIDE_EXPERTS);
+    }
+#undef GO
+    return hipGetLastError();
+}
+
 hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, int32_t *counts,
                           int32_t *offsets, int32_t *row_to_pair, int32_t *pair_to_row,
                           const uint16_t *x, int H, uint16_t *x_perm, int64_t cap, int32_t *ws,
@@ -317,13 +348,16 @@ hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, 
     const int64_t npairs = T * k;
     const int64_t nchunks = permute_chunks(T, k, El);
     const bool short_chunks = chunk_pairs(npairs, El) == 256;
-    int nbits = 0;
-    while ((1 << nbits) < El + 2) ++nbits;  // distinguishes 0..El+1
+    const int nbits = permute_bits(El);
     hipError_t err;
-    if (npairs > 0 && npairs <= SMALL_PAIRS && El <= 64 && npairs * (nbits + 2) <= SMALL_WORK) {
+    if (permute_one_workgroup(npairs, El)) {
         KernelTimer timer(kind, s);
-        permute_small_kernel<<<dim3(1), dim3(1024), 0, s>>>(ids, npairs, e0, El, nbits, counts, offsets,
-                                                             row_to_pair, pair_to_row);
+        if (El <= 64)
+            permute_small_kernel<64><<<dim3(1), dim3(1024), 0, s>>>(ids, npairs, e0, El, nbits, counts, offsets,
+                                                                     row_to_pair, pair_to_row);
+        else
+            permute_small_kernel<WIDE_EXPERTS><<<dim3(1), dim3(1024), 0, s>>>(ids, npairs, e0, El, nbits, counts,
+                                                                              offsets, row_to_pair, pair_to_row);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     } else {
         KernelTimer timer(kind, s);
@@ -336,16 +370,10 @@ hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, 
                     ids, npairs, e0, El, ws);
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
-        if (El <= 64 && nchunks > 0 && nchunks <= SCAN_SCATTER_MAX_CHUNKS) {
-            // scan and scatter in one launch
-            const unsigned blocks = (unsigned)ceil_div(nchunks, 4);
-            if (short_chunks)
-                scan_scatter_kernel<4><<<dim3(blocks), dim3(256), 0, s>>>(ids, npairs, e0, El, nbits, ws, nchunks,
-                                                                          counts, offsets, row_to_pair, pair_to_row);
-            else
-                scan_scatter_kernel<16><<<dim3(blocks), dim3(256), 0, s>>>(ids, npairs, e0, El, nbits, ws, nchunks,
-                                                                           counts, offsets, row_to_pair, pair_to_row);
-            if ((err = hipGetLastError()) != hipSuccess) return err;
+        if (scan_scatter_serves(nchunks, El)) {
+            if ((err = launch_scan_scatter(ids, T, k, e0, El, counts, offsets, row_to_pair, pair_to_row, ws, s)) !=
+                hipSuccess)
+                return err;
         } else {
             if (El <= 64) {
                 scan_narrow_kernel<<<dim3(1), dim3(1024), 0, s>>>(ws, nchunks, El, counts, offsets);
