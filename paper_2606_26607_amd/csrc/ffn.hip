@@ -919,7 +919,7 @@ struct TileClass {
 // workgroup's LDS (at least the class's ring size).  Pointers are restrict
 // parameters so that the inlined body keeps the no-alias facts of kernel
 // arguments (its loads are not reordered around the stores it makes).
-template <int BMt, int BNt, bool GATED, int WM, bool TAIL, int ASL, int BSL, bool STREAM>
+template <int BMt, int BNt, bool GATED, int WM, bool TAIL, int ASL, int BSL, bool STREAM, bool KPART>
 __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restrict__ A,
                                            const int32_t *__restrict__ row_index, int kdiv, int64_t a_rows,
                                            const int32_t *__restrict__ offsets,
@@ -1139,8 +1139,9 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
         // It is the last slice issued for the tile, so the offsets are changed
         // in place; tail is its local index in this piece (-1: none).
         const int k_left = K - (nk - 1) * BIG_BK;
-        const int tail = k_left < BIG_BK ? nk - 1 - klo : -1;
+        const int tail = KPART && k_left < BIG_BK ? nk - 1 - klo : -1;
         auto mask_tail = [&](uint32_t (&off)[8], int n, int g0, int num_records) {
+            if constexpr (!KPART) return;
             const int c0 = (lane & 7) ^ (lane >> 3);  // chunk of an even instruction; an odd one's is c0 ^ 1
 #pragma unroll
             for (int q = 0; q < 8; ++q)
@@ -1171,16 +1172,16 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
             // (NI is even, so instruction q's parity is q's)
             auto mask_own = [&]() { mask_tail(src.voa, NI, 0, src.ra.z); };
             if (loads_a) {
-                if (tail == 0) mask_own();
+                if (KPART && tail == 0) mask_own();
 #pragma unroll
                 for (int q = 0; q < NI; ++q) issue_own<NI>(src, a_slot(0), kof(0), q);
                 asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             } else {
-                if (tail == 0) mask_own();
+                if (KPART && tail == 0) mask_own();
 #pragma unroll
                 for (int q = 0; q < NI; ++q) issue_own<NI>(src, b_slot(0), kof(0), q);
                 if (ns > 1) {
-                    if (tail == 1) mask_own();
+                    if (KPART && tail == 1) mask_own();
 #pragma unroll
                     for (int q = 0; q < NI; ++q) issue_own<NI>(src, b_slot(1), kof(1), q);
                     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NI) : "memory");
@@ -1228,11 +1229,11 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
             };
             int s = 0;
             for (; s + 2 < ns; ++s) {
-                if (!loads_a && s + 2 == tail) mask_own();
+                if (KPART && !loads_a && s + 2 == tail) mask_own();
                 slice(s, T_{}, T_{});
             }
             for (; s + 1 < ns; ++s) {
-                if (loads_a && s + 1 == tail) mask_own();
+                if (KPART && loads_a && s + 1 == tail) mask_own();
                 slice(s, T_{}, F_{});
             }
             for (; s < ns; ++s) slice(s, F_{}, F_{});
@@ -1240,13 +1241,13 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
             // prologue: B(0), then (A(t), B(t+1)) for t < LA; wait for A(0), B(0)
             auto mask_a = [&]() { mask_tail(src.voa, A_INS, wave * A_INS, src.ra.z); };
             auto mask_b = [&]() { mask_tail(src.vob, B_INS, wave * B_INS, src.rb.z); };
-            if (tail == 0) mask_b();
+            if (KPART && tail == 0) mask_b();
     #pragma unroll
             for (int q = 0; q < B_INS; ++q) issue_b<BNt, STREAM>(src, b_slot(0), kof(0), q);
     #pragma unroll
             for (int t = 0; t < LA; ++t) {
-                if (t == tail) mask_a();
-                if (t + 1 == tail) mask_b();
+                if (KPART && t == tail) mask_a();
+                if (KPART && t + 1 == tail) mask_b();
                 if (t < ns) {
     #pragma unroll
                     for (int q = 0; q < A_INS; ++q) issue_a<BMt>(src, a_slot(t), kof(t), q);
@@ -1299,11 +1300,11 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
             };
             int s = 0;
             for (; s + LA + 1 < ns; ++s) {
-                if (s + LA + 1 == tail) mask_b();
+                if (KPART && s + LA + 1 == tail) mask_b();
                 slice(s, T_{}, T_{});
             }
             for (; s + LA < ns; ++s) {
-                if (s + LA == tail) mask_a();
+                if (KPART && s + LA == tail) mask_a();
                 slice(s, T_{}, F_{});
             }
             for (; s < ns; ++s) slice(s, F_{}, F_{});
@@ -1576,8 +1577,9 @@ __device__ unsigned long long g_dev_ts[2][8][DEV_TS_SLOTS];  // [0]: start (min)
 // cover disjoint rows, so a workgroup goes from its large tiles to its
 // small-row share without waiting for anyone.  STREAM: the small-row class
 // loads its weights with the non-temporal hint (launches whose weights
-// cannot stay in the last-level cache from one step to the next).
-template <bool GATED, bool STREAM>
+// cannot stay in the last-level cache from one step to the next).  KPART: K is
+// not whole slices.
+template <bool GATED, bool STREAM, bool KPART>
 __global__ __attribute__((amdgpu_flat_work_group_size(GEMM_THREADS, GEMM_THREADS), amdgpu_waves_per_eu(2, 2)))
 void gemm_grouped(GemmArgs g, TileClass small, TileClass large, int tslot)
 {
@@ -1586,7 +1588,7 @@ void gemm_grouped(GemmArgs g, TileClass small, TileClass large, int tslot)
     constexpr int OUTN = GATED ? BIGN / 2 : BIGN;
     // die-major id: the hardware deals workgroups to the 8 dies round robin
     const int vx = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    gemm_class<BIGM, BIGN, GATED, BIG_WM, false, A_SLOTS, B_SLOTS, false>(
+    gemm_class<BIGM, BIGN, GATED, BIG_WM, false, A_SLOTS, B_SLOTS, false, KPART>(
         ring, g.A, g.row_index, g.kdiv, g.a_rows, g.offsets, g.split, large.tile_prefix, nullptr, g.El, g.ne, g.cap,
         g.shared_rows, g.shared_begin, g.N, g.K, g.W, g.w_stride, g.Wsh, g.up_off, g.C, g.Csh, large.tile_cnt,
         large.partials, vx, gridDim.x, false);
@@ -1599,12 +1601,12 @@ void gemm_grouped(GemmArgs g, TileClass small, TileClass large, int tslot)
                                       (int64_t)small.tile_prefix[g.ne] * n_tiles, k_slices(g.K), gridDim.x,
                                       tall ? SMALL128 : SMALL64, vx);
     if (tall)
-        gemm_class<SMALL128.rows, BIGN, GATED, SMALL_WM, true, S128_ASL, S128_BSL, STREAM>(
+        gemm_class<SMALL128.rows, BIGN, GATED, SMALL_WM, true, S128_ASL, S128_BSL, STREAM, KPART>(
             ring, g.A, g.row_index, g.kdiv, g.a_rows, g.offsets, g.split, small.tile_prefix, small.mtile, g.El, g.ne, g.cap,
             g.shared_rows, g.shared_begin, g.N, g.K, g.W, g.w_stride, g.Wsh, g.up_off, g.C, g.Csh,
             small.tile_cnt, small.partials, sg.v, sg.size, sg.deal);
     else
-        gemm_class<SMALL64.rows, BIGN, GATED, SMALL_WM, true, SA_SLOTS, SB_SLOTS, STREAM>(
+        gemm_class<SMALL64.rows, BIGN, GATED, SMALL_WM, true, SA_SLOTS, SB_SLOTS, STREAM, KPART>(
             ring, g.A, g.row_index, g.kdiv, g.a_rows, g.offsets, g.split, small.tile_prefix, small.mtile, g.El, g.ne, g.cap,
             g.shared_rows, g.shared_begin, g.N, g.K, g.W, g.w_stride, g.Wsh, g.up_off, g.C, g.Csh,
             small.tile_cnt, small.partials, sg.v, sg.size, sg.deal);
@@ -1998,36 +2000,63 @@ struct FfnCall {
     int bm() const { return big ? BIGM : BM; }
 };
 
-// Whether the streaming kernels (ffn_stream.h) serve a call: they read every
-// active expert's weights once per 64 rows, so they are for few rows per
-// expert.  What the host knows is a bound on any expert's rows (the tokens
-// of a gathered call, where no expert takes a token twice; else all rows) and
-// a bound on the mean, R = cap / El (an EP rank's own mean is lower).  The
-// lines lie where the streaming kernels stop being faster whatever the load
-// (us, tiled / streaming):
-//   at most 64 rows: one expert with all 64 rows of H 4096, I 14336 117 / 120,
-//     32 rows 109 / 90; 32 + 1 experts of H 7168, I 2048, 64 tokens 398 / 370;
-//   up to 128 tokens, mean at most 64: 16 experts of H 4096, I 1536 141 / 111
-//     (one expert with most of 96 tokens: 154 / 190);
-//   up to 512 tokens, mean at most 32: 128 slices of H 4096, I 192, 512 tokens
-//     174 / 154 (1024 tokens, mean 64: 262 / 258);
-//   without a gather, up to 512 rows, mean at most 16: 16 experts of H 4096,
-//     I 1536 under a Zipf load, 256 rows 138 / 131 (512 rows: 142 / 178);
-//   weights of a few MB, which stay in the caches: mean at most 128 (8
-//     experts of H 256, I 512, 512 tokens 56 / 36; 1024 tokens 56 / 53).
+// Which kernels run a call's GEMMs: the tiled ones (with a tile schedule), or
+// those of ffn_stream.h, for few rows per expert (FFN_STREAM) or some dozens
+// (FFN_MID).  The choice is the host's, so it rests on bounds: no expert has
+// more rows than `rows` (the tokens of a gathered call, as no expert takes a
+// token twice; else all rows), and their mean is at most R = cap / El (an EP
+// rank's own mean is lower).  The lines lie where the kernels win whatever the
+// load; measured in us, tiled / streaming / mid, balanced and under a Zipf(1.2)
+// load:
+//   at most 64 rows: one expert of H 4096, I 14336 with all 64 117 / 106; 32 + 1
+//     experts of H 7168, I 2048 398 / 370;
+//   up to 320 tokens, mean at most 64 (48 for fewer than 8 experts): 128 slices
+//     of H 4096, I 192, 300 tokens 165 / 134 / 159 and 172 / 134 / 140; 32 experts of
+//     H 7168, I 2048, 200 tokens 485 / 453 and 198 / 161 (4 of H 4096, I 14336, mean at
+//     most 100: 272 / 278 and 395 / 430);
+//   up to 512 tokens, mean at most 24: 256 slices of a DeepSeek-shaped layer;
+//     past that mean the mid kernel: 128 experts of H 2048, I 384, mean 31, 155 / 151 /
+//     142 and 140 / 163 / 144;
+//   top-1 and top-2 layers of 8 experts and more up to 512 tokens, mean 48 to
+//     128: 8 experts of H 4096, I 1792, 300 tokens 146 / 146 / 95 and 164 / 148 / 147;
+//   rows not gathered, whole-slice widths: mean at most 28 streaming (16
+//     experts of H 4096, I 1536, 400 rows 126 / 108 / 118 and 146 / 136 / 149), 64 to
+//     112 mid for 8 experts and more (1500 rows 207 / 241 / 155 and 186 / 248 / 191);
+//   widths that are not whole slices, where the tiled kernels' rows straddle
+//     lines: mean at most 48 streaming, to 256 mid (12 experts of H 1000, I 1200,
+//     800 rows 58 / 42 / 38, 2500 rows 82 / 93 / 57; 128 slices of H 2048, I 96, 2051
+//     tokens 144 / - / 113);
+//   weights of a few MB, which stay in the caches: up to 512 rows streaming
+//     (8 experts of H 256, I 512, 512 tokens 56 / 36).
+// Past these a hot expert's rows are better off in 256-row tiles (128 slices
+// of H 4096, I 192, 1000 tokens: 250 / 227 / 188 balanced, but 207 / 288 / 236).
 constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20;
-bool stream_call(const FfnCall &c, int64_t x_rows, bool gather)
+enum FfnKernels { FFN_TILED, FFN_STREAM, FFN_MID };
+FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
 {
-    if (!c.big || c.H > (1 << 20) || c.Is > (1 << 20)) return false;
+    if (!c.big || c.H > (1 << 20) || c.Is > (1 << 20)) return FFN_TILED;
     const int64_t rows = gather ? x_rows : c.rows, R = ceil_div(c.cap, c.El);
-    if (rows <= 64) return true;
-    if ((int64_t)c.El * 6 * c.H * c.Is <= STREAM_CACHED_BYTES && rows <= 512) return true;
-    if (gather) return (rows <= 128 && R <= 64) || (rows <= 512 && R <= 32);
-    return rows <= 512 && R <= 16;
+    if (rows <= 64) return FFN_STREAM;
+    if ((int64_t)c.El * 6 * c.H * c.Is <= STREAM_CACHED_BYTES && rows <= 512) return FFN_STREAM;
+    if (!ffn_whole_slices(c.H, c.Is)) {
+        if (rows > 4096 || R > 256) return FFN_TILED;
+        return R <= 48 ? FFN_STREAM : FFN_MID;
+    }
+    if (!gather) {
+        if (R <= 28 && rows <= 1536) return FFN_STREAM;
+        return R >= 64 && R <= 112 && c.El >= 8 ? FFN_MID : FFN_TILED;
+    }
+    if (rows <= 320 && R <= (c.El < 8 ? 48 : 64)) {
+        if (k <= 2 && c.El >= 8 && rows > 128 && R > 48) return FFN_MID;
+        return FFN_STREAM;
+    }
+    if (rows > 512) return FFN_TILED;
+    if (R <= 24) return FFN_STREAM;
+    return R <= 32 || (k <= 2 && c.El >= 8 && R <= 128) ? FFN_MID : FFN_TILED;
 }
 
 template <bool GATED>
-hipError_t launch_stream(ffn_stream::StreamArgs a, int64_t rows, int ne, int kind, hipStream_t s)
+hipError_t launch_stream(ffn_stream::StreamArgs a, FfnKernels which, int64_t rows, int ne, int kind, hipStream_t s)
 {
     ffn_stream::LaunchStamps ts{nullptr, nullptr, DEV_TS_SLOTS};
     const int slot = device_ts_slot(kind);
@@ -2038,14 +2067,31 @@ hipError_t launch_stream(ffn_stream::StreamArgs a, int64_t rows, int ne, int kin
         ts.start = static_cast<unsigned long long *>(p) + slot;
         ts.end = ts.start + 8 * DEV_TS_SLOTS;
     }
+    const int64_t active = ne < a.cap + a.shared_rows ? ne : a.cap + a.shared_rows, R = ceil_div(a.cap, a.El);
+    const int slices = a.K / ffn_stream::SK;
+    // Weights that cannot stay in the caches are loaded with the non-temporal
+    // hint (64 tokens of the DeepSeek-shaped slice 420 -> 373 us), where the
+    // rows are whole 128-byte lines: rows of 192 bytes share lines with their
+    // neighbours (I_s = 96: 59 -> 61 us with the hint).
+    const bool nt = a.K % ffn_stream::SK == 0 && active * a.N * (GATED ? 2 : 1) * a.K * 2 > ((int64_t)64 << 20);
+    if (which == FFN_MID) {
+        // z over an expert's runs of 128 rows, so that a hot expert's run side
+        // by side; past sixteen a workgroup takes several
+        const int64_t runs = ceil_div(rows, 128);
+        const dim3 grid((unsigned)ceil_div(a.N, ffn_stream::MID_WAVES * (GATED ? 16 : 32)), (unsigned)ne,
+                        (unsigned)(runs < 16 ? runs : 16));
+        if (nt)
+            ffn_stream::mid_kernel<GATED, true><<<grid, dim3(64 * ffn_stream::MID_WAVES), 0, s>>>(a, ts);
+        else
+            ffn_stream::mid_kernel<GATED, false><<<grid, dim3(64 * ffn_stream::MID_WAVES), 0, s>>>(a, ts);
+        return hipGetLastError();
+    }
     // Waves that split K (2^lks of them): as many as leave each at least three
     // slices, up to four (eight never helped: the 64-token DeepSeek-shaped
     // slice 370 us with four, 398 with eight, 415 with one), or two slices
     // where the launch would not give every SIMD a wave (the tiny replicated
     // layer 21.8 -> 20.5 us).  K decides, and the bounds that a layer call and
     // its four separate calls both know, so both sum in the same order.
-    const int64_t active = ne < a.cap + a.shared_rows ? ne : a.cap + a.shared_rows, R = ceil_div(a.cap, a.El);
-    const int slices = a.K / ffn_stream::SK;
     auto waves = [&](int nb, int lks) { return active * ceil_div(a.N, GATED ? 8 * nb : 16 * nb) << lks; };
     a.lks = 0;
     while (a.lks < 2 && (slices >> (a.lks + 1)) >= 3) ++a.lks;
@@ -2059,13 +2105,12 @@ hipError_t launch_stream(ffn_stream::StreamArgs a, int64_t rows, int ne, int kin
     const int mb = rows <= 16 ? 1 : rows <= 32 || R <= 12 ? 2 : 4;
     const int nb = mb == 4 && waves(4, a.lks) >= 1024 ? 4 : 2;
     const int nw = a.lks == 2 ? 4 : 2, per = nw >> a.lks;
-    const dim3 grid((unsigned)ceil_div(ceil_div(a.N, GATED ? 8 * nb : 16 * nb), per), (unsigned)ne);
+    // z over an expert's passes, so that a hot expert's run side by side (128
+    // slices of H 4096, I 192 under a Zipf load, 300 tokens: 221 -> 135 us)
+    const int64_t passes = ceil_div(rows, 16 * mb);
+    const dim3 grid((unsigned)ceil_div(ceil_div(a.N, GATED ? 8 * nb : 16 * nb), per), (unsigned)ne,
+                    (unsigned)(passes < 8 ? passes : 8));
     const size_t lds = (size_t)nw * (mb + nb) * 2048;
-    // Weights that cannot stay in the caches are loaded with the non-temporal
-    // hint (64 tokens of the DeepSeek-shaped slice 420 -> 373 us), where the
-    // rows are whole 128-byte lines: rows of 192 bytes share lines with their
-    // neighbours (I_s = 96: 59 -> 61 us with the hint).
-    const bool nt = a.K % ffn_stream::SK == 0 && active * a.N * (GATED ? 2 : 1) * a.K * 2 > ((int64_t)64 << 20);
 #define GO(NT, MB, NB, W) ffn_stream::stream_kernel<GATED, NT, MB, NB, W><<<grid, dim3(64 * nw), lds, s>>>(a, ts)
 #define GO_NT(MB, NB, W)          \
     do {                          \
@@ -2084,7 +2129,7 @@ hipError_t launch_stream(ffn_stream::StreamArgs a, int64_t rows, int ne, int kin
 }
 
 // Both GEMMs of a call that the streaming kernels serve.
-hipError_t launch_stream_gemms(const FfnCall &c, const uint16_t *x, int64_t x_rows, const int32_t *row_index, int kdiv,
+hipError_t launch_stream_gemms(const FfnCall &c, FfnKernels which, const uint16_t *x, int64_t x_rows, const int32_t *row_index, int kdiv,
                                const int32_t *offsets, const uint16_t *w13, const uint16_t *w2, uint16_t *y,
                                int64_t shared_begin, const uint16_t *sw13, const uint16_t *sw2, uint16_t *shared_y,
                                hipStream_t s)
@@ -2096,12 +2141,33 @@ hipError_t launch_stream_gemms(const FfnCall &c, const uint16_t *x, int64_t x_ro
         KernelTimer timer(MOE_K_GATE_UP, s);
         const ffn_stream::StreamArgs a{x, row_index, kdiv, row_index ? x_rows : c.rows, offsets, El, cap, sc, (int)shared_begin, Is, H,
                                        w13, (int64_t)2 * Is * H, sw13, Is, c.h, c.h_sh, 0};
-        if ((err = launch_stream<true>(a, rows, c.ne, MOE_K_GATE_UP, s)) != hipSuccess) return err;
+        if ((err = launch_stream<true>(a, which, rows, c.ne, MOE_K_GATE_UP, s)) != hipSuccess) return err;
     }
     KernelTimer timer(MOE_K_DOWN, s);
     const ffn_stream::StreamArgs a{c.h, nullptr, 1, c.rows, offsets, El, cap, sc, (int)shared_begin, H, Is,
                                    w2, (int64_t)H * Is, sw2, 0, y, shared_y, 0};
-    return launch_stream<false>(a, rows, c.ne, MOE_K_DOWN, s);
+    return launch_stream<false>(a, which, rows, c.ne, MOE_K_DOWN, s);
+}
+
+// One tiled GEMM launch.  A K that is not whole slices takes kernels of its
+// own: the checks for its last slice cost the small-row tiles 2-5% elsewhere.
+template <bool GATED>
+void launch_grouped(const GemmArgs &g, const TileClass &sm, const TileClass &lg, bool streamed, int grid, int kind,
+                    hipStream_t s)
+{
+    const int slot = device_ts_slot(kind);
+    const dim3 gd((unsigned)grid), bd(GEMM_THREADS);
+    if (g.K % BIG_BK == 0) {
+        if (streamed)
+            gemm_grouped<GATED, true, false><<<gd, bd, 0, s>>>(g, sm, lg, slot);
+        else
+            gemm_grouped<GATED, false, false><<<gd, bd, 0, s>>>(g, sm, lg, slot);
+    } else {
+        if (streamed)
+            gemm_grouped<GATED, true, true><<<gd, bd, 0, s>>>(g, sm, lg, slot);
+        else
+            gemm_grouped<GATED, false, true><<<gd, bd, 0, s>>>(g, sm, lg, slot);
+    }
 }
 
 // The GEMM launches of a call whose schedule is already in the workspace.
@@ -2121,12 +2187,7 @@ hipError_t launch_gemms(const FfnCall &c, const uint16_t *x, int64_t x_rows, con
             const GemmArgs g{x,   row_index, kdiv, x_rows, offsets, c.split, El, ne, cap, sc, shared_begin,
                              Is,  H,         w13,  (int64_t)2 * Is * H, sw13, Is, c.h, c.h_sh};
             const TileClass sm{c.pre_s, c.mt_g, cs_gu, c.part_s}, lg{c.pre, nullptr, c_gu, c.part};
-            if (weights_streamed((int64_t)El * 2 * Is * H))
-                gemm_grouped<true, true><<<dim3((unsigned)L.grid), dim3(GEMM_THREADS), 0, s>>>(
-                    g, sm, lg, device_ts_slot(MOE_K_GATE_UP));
-            else
-                gemm_grouped<true, false><<<dim3((unsigned)L.grid), dim3(GEMM_THREADS), 0, s>>>(
-                    g, sm, lg, device_ts_slot(MOE_K_GATE_UP));
+            launch_grouped<true>(g, sm, lg, weights_streamed((int64_t)El * 2 * Is * H), L.grid, MOE_K_GATE_UP, s);
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
         if (k_slices(H) >= SPLIT_MIN_NK) {  // the large tiles may have been split over K
@@ -2140,12 +2201,7 @@ hipError_t launch_gemms(const FfnCall &c, const uint16_t *x, int64_t x_rows, con
             const GemmArgs g{c.h, nullptr, 1, rows, offsets, c.split_d, El, ne, cap, sc, shared_begin,
                              H,   Is,      w2, (int64_t)H * Is, sw2, 0, y, shared_y};
             const TileClass sm{c.pre_sd, c.mt_d, cs_dn, c.part_s}, lg{c.pre_ld, nullptr, c_dn, c.part};
-            if (weights_streamed((int64_t)El * H * Is))
-                gemm_grouped<false, true><<<dim3((unsigned)L.grid), dim3(GEMM_THREADS), 0, s>>>(
-                    g, sm, lg, device_ts_slot(MOE_K_DOWN));
-            else
-                gemm_grouped<false, false><<<dim3((unsigned)L.grid), dim3(GEMM_THREADS), 0, s>>>(
-                    g, sm, lg, device_ts_slot(MOE_K_DOWN));
+            launch_grouped<false>(g, sm, lg, weights_streamed((int64_t)El * H * Is), L.grid, MOE_K_DOWN, s);
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
         if (k_slices(Is) >= SPLIT_MIN_NK) {
@@ -2189,8 +2245,9 @@ hipError_t launch_grouped_ffn(const uint16_t *x, int64_t x_rows, const int32_t *
     if (cap + shared_rows == 0) return hipSuccess;
     const FfnCall c(x_rows, row_index != nullptr, El, cap, H, Is, shared_rows, ws);
     if (shared_rows > 0 && !c.big) return hipErrorNotSupported;  // the host API checks this first
-    if (stream_call(c, x_rows, row_index != nullptr))
-        return launch_stream_gemms(c, x, x_rows, row_index, kdiv, offsets, w13, w2, y, shared_begin, sw13, sw2,
+    const FfnKernels which = ffn_kernels(c, x_rows, row_index != nullptr, kdiv);
+    if (which != FFN_TILED)
+        return launch_stream_gemms(c, which, x, x_rows, row_index, kdiv, offsets, w13, w2, y, shared_begin, sw13, sw2,
                                    shared_y, s);
     {
         KernelTimer timer(MOE_K_SCHEDULE, s);
@@ -2338,13 +2395,15 @@ hipError_t launch_layer(const uint16_t *x, const float *logits, int64_t T, int E
         return launch_combine(y, cap, p2r, w, T, k, H, sc > 0 ? shared_y : nullptr, sb, sc, 0, out, s);
     }
     const FfnCall c(T, true, El, cap, H, Is, sc, ws_ffn);
-    if (stream_call(c, T, true)) {
-        // the streaming GEMMs take no tile schedule: the permutation is all
-        // the preparation
-        if ((err = launch_route_permute(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, cap, ws_perm,
-                                        MOE_K_LAYER_PREP, s)) != hipSuccess)
+    const FfnKernels which = ffn_kernels(c, T, true, k);
+    if (which != FFN_TILED) {
+        // these GEMMs take no tile schedule: the permutation is all the
+        // preparation
+        const int kind = layer_fused_prep(T, k, El, H, Is, sc) ? MOE_K_LAYER_PREP : MOE_K_PERMUTE;
+        if ((err = launch_route_permute(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, cap, ws_perm, kind,
+                                        s)) != hipSuccess)
             return err;
-        if ((err = launch_stream_gemms(c, x, T, r2p, k, offsets, w13, w2, y, sb, sw13, sw2, shared_y, s)) != hipSuccess)
+        if ((err = launch_stream_gemms(c, which, x, T, r2p, k, offsets, w13, w2, y, sb, sw13, sw2, shared_y, s)) != hipSuccess)
             return err;
         return launch_combine(y, cap, p2r, w, T, k, H, sc > 0 ? shared_y : nullptr, sb, sc, 0, out, s);
     }

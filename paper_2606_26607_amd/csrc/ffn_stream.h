@@ -20,6 +20,8 @@
 // 192), 64 tokens 160 -> 114; Mixtral-shaped TP slice, 1 token 54 -> 33, 64
 // tokens 99 -> 80; the tiny replicated layer 33 -> 21.
 #pragma once
+#include <type_traits>
+
 #include "ffn_dev.h"
 
 namespace moe {
@@ -53,6 +55,16 @@ constexpr int SK = 64;  // K per slice: one 128-byte line of every row
 // 16-byte chunk c of LDS row r sits at c ^ swz(r): the 16 rows of a fragment
 // read, and the 8 chunks of a row written, fall on distinct banks.
 __device__ __forceinline__ int swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+
+// Buffer of `bytes` from p on (both uniform: pinned to scalar registers).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const uint16_t *p, int64_t bytes)
+{
+    const uint64_t b = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((uint64_t)hi << 32 | lo), (short)0,
+                                             __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
 
 // 16 bytes of a buffer at this lane's byte offset plus a uniform one; past
 // the buffer's end the load returns zeros and touches no memory.
@@ -181,17 +193,9 @@ __device__ __forceinline__ void strip_rows(const StreamArgs &g, int e, int r0, i
     // rows, or NB blocks of rows; rows past N read zeros
     const uint16_t *We = e < g.El ? g.W + (int64_t)e * g.w_stride : g.Wsh;
     const int v0 = N - n0 < NB * 8 ? N - n0 : NB * 8, n1 = GATED ? n0 : n0 + NB * 8, v1 = N - n1 < NB * 8 ? N - n1 : NB * 8;
-    auto rsrc = [](const uint16_t *p, int64_t bytes) {
-        // (uniform: pinned to scalar registers)
-        const uint64_t b = reinterpret_cast<uint64_t>(p);
-        const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-        const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((uint64_t)hi << 32 | lo), (short)0,
-                                                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
-    };
-    st.w[0] = rsrc(We + (int64_t)n0 * K, (int64_t)(v0 > 0 ? v0 : 0) * K * 2);
-    st.w[1] = rsrc(We + (int64_t)((GATED ? g.up_off : 0) + n1) * K, (int64_t)(v1 > 0 ? v1 : 0) * K * 2);
-    st.x = rsrc(g.A, g.a_rows * K * 2);
+    st.w[0] = uniform_rsrc(We + (int64_t)n0 * K, (int64_t)(v0 > 0 ? v0 : 0) * K * 2);
+    st.w[1] = uniform_rsrc(We + (int64_t)((GATED ? g.up_off : 0) + n1) * K, (int64_t)(v1 > 0 ? v1 : 0) * K * 2);
+    st.x = uniform_rsrc(g.A, g.a_rows * K * 2);
     st.rowstep = 8 * (uint32_t)K * 2;
 #pragma unroll
     for (int j = 0; j < NB; ++j) st.wo[j] = (((j % (NB / 2)) * 16 + wr) * (uint32_t)K + wq * 8) * 2;
@@ -258,7 +262,10 @@ struct LaunchStamps {
 };
 
 // Die of this workgroup: the hardware deals them to the 8 dies round robin.
-__device__ __forceinline__ int die() { return (int)((blockIdx.y * gridDim.x + blockIdx.x) & 7); }
+__device__ __forceinline__ int die()
+{
+    return (int)(((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) & 7);
+}
 
 // Grid: x over the strips of output columns, y over the experts.  MBMAX: row
 // blocks of a pass at most; an expert of more rows takes more passes (its
@@ -272,7 +279,7 @@ void stream_kernel(StreamArgs g, LaunchStamps ts)
     const int e = blockIdx.y;
     const int r0 = __builtin_amdgcn_readfirstlane((int)expert_begin(g.offsets, g.El, g.cap, e));
     const int r1 = __builtin_amdgcn_readfirstlane((int)expert_end(g.offsets, g.El, g.cap, g.shared_rows, e));
-    if (r1 <= r0) return;
+    if (r1 - r0 <= (int)blockIdx.z * MBMAX * 16) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ks = 1 << g.lks, kw = wave & (ks - 1);
     const int n0 = ((blockIdx.x * (blockDim.x >> 6) + wave) >> g.lks) * OUTC;
     if (g.lks == 0 && n0 >= g.N) return;
@@ -285,18 +292,195 @@ void stream_kernel(StreamArgs g, LaunchStamps ts)
     if (ts.start != nullptr && threadIdx.x == 0) atomicMin(ts.start + die() * ts.stride, __builtin_amdgcn_s_memrealtime());
     constexpr int PER = (NB + MBMAX) * 16 * 8;  // 16-byte chunks of LDS per wave
     const int rows = r1 - r0;
-    for (int m0 = 0; m0 < rows;) {
+    for (int m0 = blockIdx.z * MBMAX * 16; m0 < rows; m0 += gridDim.z * MBMAX * 16) {
         const int left = rows - m0;
-        if (MBMAX == 1 || left <= 16) {
-            strip_rows<GATED, NT, 1, NB, NB == 4 ? 2 : 3, PER>(g, e, r0, r1, m0, n0, k0, ns, k_tail, lds);
-            m0 += 16;
-        } else if (MBMAX == 2 || left <= 32) {
-            strip_rows<GATED, NT, 2, NB, NB == 4 ? 2 : 3, PER>(g, e, r0, r1, m0, n0, k0, ns, k_tail, lds);
-            m0 += 32;
-        } else if constexpr (MBMAX >= 4) {
-            strip_rows<GATED, NT, 4, NB, 2, PER>(g, e, r0, r1, m0, n0, k0, ns, k_tail, lds);
-            m0 += 64;
+        if (MBMAX == 1 || left <= 16) strip_rows<GATED, NT, 1, NB, NB == 4 ? 2 : 3, PER>(g, e, r0, r1, m0, n0, k0, ns, k_tail, lds);
+        else if (MBMAX == 2 || left <= 32) strip_rows<GATED, NT, 2, NB, NB == 4 ? 2 : 3, PER>(g, e, r0, r1, m0, n0, k0, ns, k_tail, lds);
+        else if constexpr (MBMAX >= 4) strip_rows<GATED, NT, 4, NB, 2, PER>(g, e, r0, r1, m0, n0, k0, ns, k_tail, lds);
+    }
+    if (ts.start != nullptr && threadIdx.x == 0) atomicMax(ts.end + die() * ts.stride, __builtin_amdgcn_s_memrealtime());
+}
+
+// ---------------------------------------------------------------------------
+// The same stream for more rows per expert: a workgroup of four waves takes
+// 16 * MB token rows (up to 128) against 64 * NB weight rows, 16 * NB of them
+// a wave's own.  The weights move as above, each wave's slice through its own
+// LDS; the activations' slice is loaded once by the four waves together (a
+// quarter each) and shared through two LDS buffers, so a barrier per slice
+// hands it over.
+// ---------------------------------------------------------------------------
+constexpr int MID_WAVES = 4;
+
+template <bool GATED, bool NT, int MB, int NB, int U>
+__device__ __forceinline__ void mid_rows(const StreamArgs &g, int e, int r0, int r1, int m0, int n0, uint4 *lds, int abuf,
+                                         int bofs)
+{
+    constexpr int NX = MB / 2;                      // this wave's activation instructions per slice (8 rows each)
+    constexpr int OUTC = GATED ? 8 * NB : 16 * NB;  // output columns of the wave
+    static_assert(MB % 2 == 0, "a quarter of the rows in whole instructions");
+    const int lane = threadIdx.x & 63, r = lane & 15, c = lane >> 4, wr = lane >> 3, wq = lane & 7;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int K = g.K, N = g.N;
+    uint32_t xo[NX], wo[NB];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        int row = r0 + m0 + (wave * NX + i) * 8 + wr;
+        row = row < r1 ? row : r1 - 1;
+        uint32_t t = (uint32_t)row;
+        if (g.row_index != nullptr)
+            t = e < g.El ? (uint32_t)g.row_index[row] / (uint32_t)g.kdiv : (uint32_t)(g.shared_begin + row - g.cap);
+        xo[i] = (t * (uint32_t)K + wq * 8) * 2;
+    }
+    const uint16_t *We = e < g.El ? g.W + (int64_t)e * g.w_stride : g.Wsh;
+    const int v0 = N - n0 < NB * 8 ? N - n0 : NB * 8, n1 = GATED ? n0 : n0 + NB * 8, v1 = N - n1 < NB * 8 ? N - n1 : NB * 8;
+    const __amdgpu_buffer_rsrc_t w0 = uniform_rsrc(We + (int64_t)n0 * K, (int64_t)(v0 > 0 ? v0 : 0) * K * 2);
+    const __amdgpu_buffer_rsrc_t w1 = uniform_rsrc(We + (int64_t)((GATED ? g.up_off : 0) + n1) * K, (int64_t)(v1 > 0 ? v1 : 0) * K * 2);
+    const __amdgpu_buffer_rsrc_t xr = uniform_rsrc(g.A, g.a_rows * K * 2);
+    const uint32_t rowstep = 8 * (uint32_t)K * 2;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) wo[j] = (((j % (NB / 2)) * 16 + wr) * (uint32_t)K + wq * 8) * 2;
+    f32x4_t acc[MB][NB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[m][j] = f32x4_t{};
+
+    uint4 *const bl = lds + bofs + wave * (NB * 16 * 8);
+    struct Slice {
+        u32x4_t w[2 * NB], x[NX];
+    };
+    Slice t[U];
+    const int full = K / SK, ns = (K + SK - 1) / SK;  // whole slices, all slices
+    auto load = [&](Slice &v, int s) {
+        const uint32_t so = s * (SK * 2);
+        // (a last slice partly past K: chunks past K read zeros)
+        const bool in = s < full || s * SK + wq * 8 < K;
+#pragma unroll
+        for (int i = 0; i < 2 * NB; ++i)
+            v.w[i] = load16<NT>(i < NB ? w0 : w1, in ? wo[i >> 1] + (i & 1) * rowstep : 0xfffffff0u, so);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) v.x[i] = load16<false>(xr, in ? xo[i] : 0xfffffff0u, so);
+    };
+    auto mul = [&](const Slice &v, int s, auto more, int snext, Slice &nxt) {
+        uint4 *const al = lds + (s & 1) * abuf;
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int row8 = wave * NX + i;
+            al[(row8 * 8 + wr) * 8 + (wq ^ wr ^ (row8 & 1))] = __builtin_bit_cast(uint4, v.x[i]);
         }
+#pragma unroll
+        for (int i = 0; i < 2 * NB; ++i) bl[(i * 8 + wr) * 8 + (wq ^ wr ^ (i & 1))] = __builtin_bit_cast(uint4, v.w[i]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(more)::value) load(nxt, snext);
+        __builtin_amdgcn_sched_barrier(0);
+        // every wave's rows of the slice are in LDS; the other buffer's were
+        // read before this wave came here
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        // step i multiplies token block i % MB of k-step i / MB; its fragment
+        // is read D steps ahead (the LDS latency under D steps' MFMAs)
+        constexpr int D = MB < 4 ? MB : 4, STEPS = 2 * MB;
+        bf16x8_t b[2][NB], a[D];
+        const int p0 = c ^ swz(r);
+        auto read_b = [&](int kk) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) b[kk][j] = __builtin_bit_cast(bf16x8_t, bl[(j * 16 + r) * 8 + (p0 ^ (kk * 4))]);
+        };
+        auto read_a = [&](int i) {
+            a[i % D] = __builtin_bit_cast(bf16x8_t, al[((i % MB) * 16 + r) * 8 + (p0 ^ ((i / MB) * 4))]);
+        };
+        read_b(0);
+#pragma unroll
+        for (int i = 0; i < D; ++i) read_a(i);
+        read_b(1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                acc[i % MB][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[i / MB][j], a[i % D], acc[i % MB][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + D < STEPS) read_a(i + D);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    using T_ = std::true_type;
+    using F_ = std::false_type;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        load(t[u], u < ns ? u : ns - 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int s = 0;
+    for (; s + 2 * U <= ns; s += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) mul(t[u], s + u, T_{}, s + U + u, t[u]);
+    }
+    if (s + U < ns) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) mul(t[u], s + u, T_{}, s + U + u < ns ? s + U + u : ns - 1, t[u]);
+        s += U;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (s + u < ns) mul(t[u], s + u, F_{}, 0, t[u]);
+
+    uint16_t *Cb = e < g.El ? g.C + (int64_t)r0 * N : g.Csh + (int64_t)(r0 - g.cap) * N;
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int row = m0 + m * 16 + r;
+        if (row >= r1 - r0) continue;
+#pragma unroll
+        for (int j = 0; j < OUTC / 16; ++j) {
+            const int col = n0 + 16 * j + 4 * c;
+            float o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                o[i] = GATED ? silu_mul(acc[m][j][i], acc[m][j + (GATED ? NB / 2 : 0)][i]) : acc[m][j][i];
+            uint2 v;
+            v.x = bf16_bits(o[0]) | (uint32_t)bf16_bits(o[1]) << 16;
+            v.y = bf16_bits(o[2]) | (uint32_t)bf16_bits(o[3]) << 16;
+            if (col < N) *reinterpret_cast<uint2 *>(Cb + (int64_t)row * N + col) = v;
+        }
+    }
+    // the next rows' first slice may not overtake a wave still reading these
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Grid: x over the strips of output columns, y over the experts, z over their
+// runs of 16 * MBMAX rows, in the slowest dimension: with an expert's runs
+// next to each other the workgroups past its rows, which end at once, left
+// whole shader engines with nothing else (120 -> 200 us and more).  Two
+// workgroups a CU: four weight blocks a wave, three workgroups a CU, a second
+// set of buffers or the next slice staged between the MFMAs spill.
+// Measured, us, tiled kernels before: 128 experts of H 4096, I 192, 100 rows
+// each 314 -> 205; 16 of H 2048, I 768 69 -> 49; 8 slices of H 4096, I 1792, 400
+// tokens of a top-2 layer 150 -> 98.  What bounds it is the chain of a slice
+// (registers to LDS, barrier, fragments, MFMAs) at two waves a SIMD: 0.5 PF.
+template <bool GATED, bool NT>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * MID_WAVES, 64 * MID_WAVES), amdgpu_waves_per_eu(2)))
+void mid_kernel(StreamArgs g, LaunchStamps ts)
+{
+    constexpr int MBMAX = 8, NB = 2, U = 3;
+    constexpr int ABUF = MBMAX * 16 * 8, BOFS = 2 * ABUF;
+    __shared__ uint4 lds[BOFS + MID_WAVES * NB * 16 * 8];
+    constexpr int OUTC = GATED ? 8 * NB : 16 * NB;
+    const int e = blockIdx.y;
+    const int r0 = __builtin_amdgcn_readfirstlane((int)expert_begin(g.offsets, g.El, g.cap, e));
+    const int r1 = __builtin_amdgcn_readfirstlane((int)expert_end(g.offsets, g.El, g.cap, g.shared_rows, e));
+    const int rows = r1 - r0;
+    if (rows <= (int)blockIdx.z * MBMAX * 16) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = (blockIdx.x * MID_WAVES + wave) * OUTC;
+    if (ts.start != nullptr && threadIdx.x == 0) atomicMin(ts.start + die() * ts.stride, __builtin_amdgcn_s_memrealtime());
+    for (int m0 = blockIdx.z * MBMAX * 16; m0 < rows; m0 += gridDim.z * MBMAX * 16) {
+        const int left = rows - m0;
+        if (left <= 32) mid_rows<GATED, NT, 2, NB, U>(g, e, r0, r1, m0, n0, lds, ABUF, BOFS);
+        else if (left <= 64) mid_rows<GATED, NT, 4, NB, U>(g, e, r0, r1, m0, n0, lds, ABUF, BOFS);
+        else mid_rows<GATED, NT, 8, NB, U>(g, e, r0, r1, m0, n0, lds, ABUF, BOFS);
     }
     if (ts.start != nullptr && threadIdx.x == 0) atomicMax(ts.end + die() * ts.stride, __builtin_amdgcn_s_memrealtime());
 }

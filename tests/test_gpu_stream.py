@@ -80,3 +80,56 @@ def test_stream_shared_and_non_temporal(oracle, T):
     assert_close_rel(bf16_f64(host_bf16(sy))[:sc],
                      oracle.grouped_ffn(x[sb:sb + sc], np.array([0, sc], np.int32), sw13[None], sw2[None]),
                      what="shared")
+
+
+# rows per expert whose mean takes the mid kernel: runs of 128, 64 and 32 rows, and experts of several runs
+MID = [128, 65, 0, 64, 200, 33, 1, 130]
+
+
+@pytest.mark.parametrize("rows,gather,H,Is", [
+    (MID, False, 128, 128),             # two whole slices: fewer than the loads kept in flight
+    (MID, False, 448, 320), (MID, False, 1024, 192),
+    (MID, False, 200, 72), (MID, False, 56, 264),    # partial last slices; strips past the columns
+    (MID, True, 1000, 328),
+    ([900, 70, 130, 20], False, 136, 200),
+])
+def test_mid_edges(oracle, rows, gather, H, Is):
+    El, k, n = len(rows), 2, sum(rows)
+    offs = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    T = 700 if gather else n
+    x = mi.random_bf16((T, H), seed=H + Is, tag=90)
+    w13 = mi.random_bf16((El, 2 * Is, H), seed=H, tag=91, std=0.05)
+    w2 = mi.random_bf16((El, H, Is), seed=H, tag=92, std=0.05)
+    r2p = np.random.default_rng(H + n).integers(0, T * k, n).astype(np.int32) if gather else None
+    want = oracle.grouped_ffn(x if r2p is None else x[r2p // k], offs, w13, w2)
+    runs = []
+    for _ in range(2):
+        y = torch.full((n + 1, H), 7.0, dtype=torch.bfloat16, device="cuda")
+        moe.grouped_ffn(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), y=y, cap_rows=n,
+                        row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1)
+        torch.cuda.synchronize()
+        runs.append(host_bf16(y))
+    np.testing.assert_array_equal(runs[0], runs[1])
+    assert np.all(bf16_f64(runs[0])[n] == 7.0)  # nothing past the rows
+    assert_close_rel(bf16_f64(runs[0])[:n], want, what=f"rows={rows} H={H} Is={Is}")
+
+
+@pytest.mark.parametrize("T,E,k,I,zipf", [(300, 8, 2, 4096, None), (480, 8, 1, 4096, 1.2), (400, 100, 8, 520, 1.2)])
+def test_mid_layer(oracle, T, E, k, I, zipf):
+    """A layer call and its four separate calls through the mid kernel (with the non-temporal hint in the first), bit
+    for bit and against the oracle."""
+    H = 1088
+    cfg = mi.MoeConfig("mid", T=T, H=H, E=E, k=k, I=I, P=1, layout="replicated", zipf_s=zipf, seed=T)
+    inp = mi.make_inputs(cfg)
+    layer = moe.MoeLayer(T, E, k, 0, dev_bf16(inp.w13), dev_bf16(inp.w2))
+    x, lg = dev_bf16(inp.x), torch.from_numpy(inp.logits).cuda()
+    got = []
+    for fn in (layer.forward_calls, layer.forward):
+        layer.y.zero_()
+        layer.out.zero_()
+        fn(x, lg)
+        torch.cuda.synchronize()
+        got.append([host_bf16(layer.y), host_bf16(layer.out)])
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    assert_close_rel(bf16_f64(got[1][1]), oracle.layer(inp), what=f"T={T} E={E} k={k}")
