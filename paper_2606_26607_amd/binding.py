@@ -108,9 +108,19 @@ def _check(status: int) -> None:
         raise MoeError(status, L.moe_status_str(status).decode(), L.moe_last_error().decode())
 
 
+# The current stream's handle on the current device, without the Stream object
+# that torch.cuda.current_stream() makes (2.7 us of a 10 us call); builds of
+# torch that lack these two take that way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None) -> Optional[int]:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream or None
+    if stream is not None:
+        return stream.cuda_stream or None
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream or None
+    return _raw_stream(_raw_device()) or None
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -122,7 +132,7 @@ def _need(t: torch.Tensor, dtype, name: str, ndim: Optional[int] = None) -> None
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be on the GPU")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
@@ -163,15 +173,17 @@ def permute(topk_ids: torch.Tensor, E: int, expert_begin: int, n_local: int,
     dev = topk_ids.device
     cap = T * min(k, n_local)
     o = dict(out or {})
-    o.setdefault("counts", torch.empty(n_local, dtype=torch.int32, device=dev))
-    o.setdefault("offsets", torch.empty(n_local + 1, dtype=torch.int32, device=dev))
-    o.setdefault("row_to_pair", torch.empty(max(cap, 1), dtype=torch.int32, device=dev))
-    o.setdefault("pair_to_row", torch.empty(max(T * k, 1), dtype=torch.int32, device=dev))
+    # (only what the caller did not bring is allocated)
+    for name, n in (("counts", n_local), ("offsets", n_local + 1), ("row_to_pair", cap or 1),
+                    ("pair_to_row", T * k or 1)):
+        if name not in o:
+            o[name] = torch.empty(n, dtype=torch.int32, device=dev)
     H = 0
     if x is not None and gather:
         _need(x, torch.bfloat16, "x", 2)
         H = x.shape[1]
-        o.setdefault("x_perm", torch.empty((max(cap, 1), H), dtype=torch.bfloat16, device=dev))
+        if "x_perm" not in o:
+            o["x_perm"] = torch.empty((max(cap, 1), H), dtype=torch.bfloat16, device=dev)
     else:
         o["x_perm"] = None
     if workspace is None:
