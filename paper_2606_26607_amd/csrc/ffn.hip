@@ -2023,14 +2023,15 @@ struct FfnCall {
 //     experts of H 4096, I 1536, 400 rows 126 / 108 / 118 and 146 / 136 / 149), 64 to
 //     112 mid for 8 experts and more (1500 rows 207 / 241 / 155 and 186 / 248 / 191);
 //   widths that are not whole slices, where the tiled kernels' rows straddle
-//     lines: mean at most 48 streaming, to 256 mid (12 experts of H 1000, I 1200,
-//     800 rows 58 / 42 / 38, 2500 rows 82 / 93 / 57; 128 slices of H 2048, I 96, 2051
-//     tokens 144 / - / 113);
+//     lines: mean at most 48 streaming, to 96 mid, to 256 where an expert's
+//     weights are a few MB (12 experts of H 1000, I 1200, 800 rows 58 / 42 / 38,
+//     2500 rows 82 / 93 / 57; 128 slices of H 2048, I 96, 2051 tokens 143 / - / 121;
+//     but 96 of H 3608, I 480, 1656 tokens, mean 138, 423 / - / 527);
 //   weights of a few MB, which stay in the caches: up to 512 rows streaming
 //     (8 experts of H 256, I 512, 512 tokens 56 / 36).
 // Past these a hot expert's rows are better off in 256-row tiles (128 slices
 // of H 4096, I 192, 1000 tokens: 250 / 227 / 188 balanced, but 207 / 288 / 236).
-constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20;
+constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20, RAGGED_SMALL_BYTES = (int64_t)8 << 20;
 enum FfnKernels { FFN_TILED, FFN_STREAM, FFN_MID };
 FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
 {
@@ -2039,7 +2040,7 @@ FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
     if (rows <= 64) return FFN_STREAM;
     if ((int64_t)c.El * 6 * c.H * c.Is <= STREAM_CACHED_BYTES && rows <= 512) return FFN_STREAM;
     if (!ffn_whole_slices(c.H, c.Is)) {
-        if (rows > 4096 || R > 256) return FFN_TILED;
+        if (rows > 4096 || R > ((int64_t)6 * c.H * c.Is <= RAGGED_SMALL_BYTES ? 256 : 96)) return FFN_TILED;
         return R <= 48 ? FFN_STREAM : FFN_MID;
     }
     if (!gather) {
