@@ -292,10 +292,11 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint16_t *__restrict_
     }
 }
 
-// Outputs above this are stored past the caches (2048 tokens of H 7168 to 8
-// rows each, 235 MB: 93.7 us with routing and permutation before, 74.6 by
-// token, 66.1 with the hint; 1000 tokens 51.4, 43.1, 38.7; 2048 of H 2048, 67 MB,
-// 39.1, 26.9, 28.2).
+// Outputs above this are stored past the caches.  Routing, permutation and
+// gather, us with cached / non-temporal stores: 2048 tokens of H 7168 to 8 rows
+// each (235 MB) 74.6 / 66.1, 1000 tokens (115 MB) 43.1 / 38.7, 8192 tokens of H 4096
+// to 2 (134 MB) 49.0 / 40.3; but 2048 of H 2048 to 8 (67 MB) 26.9 / 28.2.  By output
+// row the first took 88.8.
 constexpr int64_t GATHER_CACHED_BYTES = (int64_t)80 << 20;
 
 // Scratch of the allocation-free entry point: the per-chunk histograms that

@@ -36,6 +36,25 @@ def test_permute_wide(oracle, T, E, k, e0, El):
     np.testing.assert_array_equal(o["pair_to_row"].cpu().numpy()[:T * k], p2r)
 
 
+@pytest.mark.parametrize("T,H,E,k,e0,El", [
+    (0, 64, 8, 2, 0, 8),                                # no tokens: nothing written
+    (1, 8, 16, 16, 0, 16), (300, 8, 8, 2, 2, 2),        # one vector a row; tokens with no row here
+    (77, 520, 32, 16, 5, 9), (50, 2040, 8, 3, 0, 8),    # last chunk partly filled; one vector below a whole one
+    (33, 2056, 8, 2, 4, 4), (20000, 64, 8, 4, 0, 8),    # second chunk of one vector; several tokens a workgroup
+    (1281, 4096, 16, 8, 0, 16), (1280, 4096, 16, 8, 0, 16)])  # either side of the 80 MiB of cached stores
+def test_gather(T, H, E, k, e0, El):
+    """The gathered rows are the tokens' own, bit for bit; rows past the last one stay as they were."""
+    x = torch.randint(-2 ** 15, 2 ** 15, (T, H), dtype=torch.int16, device="cuda").view(torch.bfloat16)
+    ids = torch.from_numpy(mi.random_topk_ids(T, E, k, seed=T + H) if T else np.zeros((0, k), np.int32)).cuda()
+    xp = torch.full((max(T * k, 4), H), -7, dtype=torch.int16, device="cuda")
+    o = moe.permute(ids, E, e0, El, x=x, out={"x_perm": xp.view(torch.bfloat16)})
+    n = int(o["offsets"][-1])
+    assert n == int(((ids >= e0) & (ids < e0 + El)).sum())
+    rows = o["row_to_pair"][:n].long() // k
+    assert torch.equal(xp[:n], x.view(torch.int16)[rows])
+    assert bool((xp[n:] == -7).all())
+
+
 @pytest.mark.parametrize("T,E,k,layout,P", [
     (1, 8, 2, "replicated", 1), (64, 8, 2, "replicated", 1), (128, 16, 1, "ep", 2),   # routed in the workgroup
     (16, 64, 2, "ep", 2), (17, 32, 2, "replicated", 1), (5, 128, 2, "replicated", 1), (3, 256, 4, "replicated", 1),
