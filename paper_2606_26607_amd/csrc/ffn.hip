@@ -25,7 +25,7 @@ namespace {
 
 using namespace ffn_dev;
 
-constexpr int BM = 64, BN = 64, BK = 64;  // the general kernel (operands past 32-bit byte offsets)
+constexpr int BM = 64, BN = 64, BK = 64;  // the general kernel (operands past 32-bit byte offsets, ffn_narrow)
 constexpr int KCH = BK / 8;               // 16-byte chunks per tile row
 
 // A read of metadata that earlier launches wrote and the grouped GEMM only
@@ -1961,6 +1961,17 @@ bool ffn_large_tiles(int64_t x_rows, int64_t rows, int H, int Is)
 
 namespace {
 
+// Many rows of experts with a few hundred KB of weights, in widths that are
+// not whole slices: most of a 256-wide tile would be padding, and the general
+// kernel's 64x64 tiles take less (us, tiled / general, balanced and under a
+// Zipf(1.2) load, 6000 tokens: 16 experts of H 208, I 32 60 / 50 and 62 / 50, 8 of
+// H 72, I 40 48 / 32 and 49 / 35, 64 of H 520, I 72 87 / 86 and 90 / 84; but 12 of
+// H 1000, I 200, 1.2 MB, 98 / 170).  Up to 4096 rows ffn_kernels chooses.
+bool ffn_narrow(int64_t rows, int H, int Is)
+{
+    return !ffn_whole_slices(H, Is) && rows > 4096 && (int64_t)6 * H * Is <= (int64_t)256 << 10;
+}
+
 // One grouped-FFN call: its row space (the routed rows [0, cap), then the
 // shared expert's rows), the workspace parts and the schedule's arguments.
 struct FfnCall {
@@ -1992,7 +2003,7 @@ struct FfnCall {
         part = reinterpret_cast<float *>(base + L.off_part);
         h = reinterpret_cast<uint16_t *>(base + L.off_h);
         h_sh = h + cap * Is;  // the shared expert's h rows
-        big = ffn_large_tiles(gather ? x_rows : rows, rows, H, Is);
+        big = ffn_large_tiles(gather ? x_rows : rows, rows, H, Is) && !ffn_narrow(gather ? x_rows : rows, H, Is);
         n_cnt = big ? L.t_gu + L.t_dn + L.ts_gu + L.ts_dn : 0;
         sh = sched_shape(H, Is, L.grid);
         so = SchedOut{{pre, pre_ld}, {pre_s, pre_sd}, {split, split_d}, {mt_g, mt_d}};
@@ -2026,12 +2037,17 @@ struct FfnCall {
 //     lines: mean at most 48 streaming, to 96 mid, to 256 where an expert's
 //     weights are a few MB (12 experts of H 1000, I 1200, 800 rows 58 / 42 / 38,
 //     2500 rows 82 / 93 / 57; 128 slices of H 2048, I 96, 2051 tokens 143 / - / 121;
-//     but 96 of H 3608, I 480, 1656 tokens, mean 138, 423 / - / 527);
+//     but 96 of H 3608, I 480, 1656 tokens, mean 138, 423 / - / 527); up to 2 MB
+//     and 3072 tokens mid at any mean (12 slices of H 1000, I 200, 2500 tokens
+//     83 / 87 / 64, Zipf 83 / 107 / 88, 98 in the general kernel, 935 tokens
+//     79 / 49 / 43 and 74 / 55 / 52; 10 of H 328, I 808, 2500 tokens 72 / 73 / 51
+//     and 77 / 84 / 63);
 //   weights of a few MB, which stay in the caches: up to 512 rows streaming
 //     (8 experts of H 256, I 512, 512 tokens 56 / 36).
 // Past these a hot expert's rows are better off in 256-row tiles (128 slices
 // of H 4096, I 192, 1000 tokens: 250 / 227 / 188 balanced, but 207 / 288 / 236).
-constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20, RAGGED_SMALL_BYTES = (int64_t)8 << 20;
+constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20, RAGGED_SMALL_BYTES = (int64_t)8 << 20,
+                  RAGGED_MID_BYTES = (int64_t)2 << 20, RAGGED_MID_ROWS = 3072;
 enum FfnKernels { FFN_TILED, FFN_STREAM, FFN_MID };
 FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
 {
@@ -2040,7 +2056,9 @@ FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
     if (rows <= 64) return FFN_STREAM;
     if ((int64_t)c.El * 6 * c.H * c.Is <= STREAM_CACHED_BYTES && rows <= 512) return FFN_STREAM;
     if (!ffn_whole_slices(c.H, c.Is)) {
-        if (rows > 4096 || R > ((int64_t)6 * c.H * c.Is <= RAGGED_SMALL_BYTES ? 256 : 96)) return FFN_TILED;
+        const int64_t bytes = (int64_t)6 * c.H * c.Is;  // an expert's weights
+        if (rows <= RAGGED_MID_ROWS && bytes <= RAGGED_MID_BYTES) return R <= 48 ? FFN_STREAM : FFN_MID;
+        if (rows > 4096 || R > (bytes <= RAGGED_SMALL_BYTES ? 256 : 96)) return FFN_TILED;
         return R <= 48 ? FFN_STREAM : FFN_MID;
     }
     if (!gather) {

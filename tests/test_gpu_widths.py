@@ -46,6 +46,40 @@ def test_partial_last_slice(oracle, H, Is, gather):
     assert_close_rel(bf16_f64(host_bf16(y)), ref, what=f"H={H} Is={Is} gather={gather}")
 
 
+@pytest.mark.parametrize("H,Is,rows", [
+    (208, 32, [2500, 0, 300, 1]),                        # mid kernel, more 128-row runs than its grid holds
+    (1000, 328, [3000, 72]), (1000, 328, [3000, 73]),    # either side of its rows: mid, tiled
+    (1000, 352, [500, 300]),                             # weights just above its size: tiled
+    (208, 32, [4000, 96]), (208, 32, [4000, 97]),        # tiled; the general kernel past it
+    (72, 40, [4100, 0, 5]), (8, 8, [5000])])
+def test_small_weights_many_rows(oracle, H, Is, rows):
+    n = sum(rows)
+    offs = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    x = mi.random_bf16((n, H), seed=H, tag=79)
+    w13 = mi.random_bf16((len(rows), 2 * Is, H), seed=H, tag=71, std=0.05)
+    w2 = mi.random_bf16((len(rows), H, Is), seed=H, tag=72, std=0.05)
+    y = moe.grouped_ffn(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2))
+    torch.cuda.synchronize()
+    assert_close_rel(bf16_f64(host_bf16(y)), oracle.grouped_ffn(x, offs, w13, w2), what=f"H={H} Is={Is} {rows}")
+
+
+@pytest.mark.parametrize("T,H,I", [(935, 208, 32), (3072, 72, 40), (4200, 72, 40)])
+def test_small_weights_layer(oracle, T, H, I):
+    """One call and four calls choose the same kernels: equal bits."""
+    cfg = mi.MoeConfig("narrow", T=T, H=H, E=16, k=8, I=I, P=1, layout="replicated", rank=0, seed=T)
+    inp = mi.make_inputs(cfg)
+    layer = moe.MoeLayer(T, 16, 8, 0, dev_bf16(inp.w13), dev_bf16(inp.w2))
+    x, lg = dev_bf16(inp.x), torch.from_numpy(inp.logits).cuda()
+    got = []
+    for fn in (layer.forward_calls, layer.forward):
+        layer.out.view(torch.uint8).fill_(0xA5)
+        fn(x, lg)
+        torch.cuda.synchronize()
+        got.append(host_bf16(layer.out).copy())
+    np.testing.assert_array_equal(*got)
+    assert_close_rel(bf16_f64(got[0]), oracle.layer(inp), what=f"T={T} H={H} I={I}")
+
+
 def test_infinite_neighbour(oracle):
     """A row's neighbour in memory holds infinities: they stay out of the row's own result."""
     H, Is, n = 200, 72, 300
