@@ -66,6 +66,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const uint16_t *p
                                              __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
 
+// Rows [row, row + n) of a weight block with rows of K values.  A part wholly
+// past the block (n <= 0) gets the block's first row instead, whose products
+// belong to columns that are not stored: a load's uniform offset along K is at
+// most a row, so no range is shorter than it, whether the bounds check leaves
+// that offset out or takes it off the range.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const uint16_t *W, int64_t row, int n, int K)
+{
+    return uniform_rsrc(n > 0 ? W + row * K : W, (int64_t)(n > 0 ? n : 1) * K * 2);
+}
+
 // 16 bytes of a buffer at this lane's byte offset plus a uniform one; past
 // the buffer's end the load returns zeros and touches no memory.
 template <bool NT>
@@ -190,11 +200,12 @@ __device__ __forceinline__ void strip_rows(const StreamArgs &g, int e, int r0, i
         st.xo[i] = (t * (uint32_t)K + wq * 8) * 2;
     }
     // the strip's weight rows: NB/2 blocks of gate rows and the matching up
-    // rows, or NB blocks of rows; rows past N read zeros
+    // rows, or NB blocks of rows; rows past N read zeros (or the block's first
+    // row) and are not stored
     const uint16_t *We = e < g.El ? g.W + (int64_t)e * g.w_stride : g.Wsh;
     const int v0 = N - n0 < NB * 8 ? N - n0 : NB * 8, n1 = GATED ? n0 : n0 + NB * 8, v1 = N - n1 < NB * 8 ? N - n1 : NB * 8;
-    st.w[0] = uniform_rsrc(We + (int64_t)n0 * K, (int64_t)(v0 > 0 ? v0 : 0) * K * 2);
-    st.w[1] = uniform_rsrc(We + (int64_t)((GATED ? g.up_off : 0) + n1) * K, (int64_t)(v1 > 0 ? v1 : 0) * K * 2);
+    st.w[0] = rows_rsrc(We, n0, v0, K);
+    st.w[1] = rows_rsrc(We, (GATED ? g.up_off : 0) + n1, v1, K);
     st.x = uniform_rsrc(g.A, g.a_rows * K * 2);
     st.rowstep = 8 * (uint32_t)K * 2;
 #pragma unroll
@@ -333,8 +344,8 @@ __device__ __forceinline__ void mid_rows(const StreamArgs &g, int e, int r0, int
     }
     const uint16_t *We = e < g.El ? g.W + (int64_t)e * g.w_stride : g.Wsh;
     const int v0 = N - n0 < NB * 8 ? N - n0 : NB * 8, n1 = GATED ? n0 : n0 + NB * 8, v1 = N - n1 < NB * 8 ? N - n1 : NB * 8;
-    const __amdgpu_buffer_rsrc_t w0 = uniform_rsrc(We + (int64_t)n0 * K, (int64_t)(v0 > 0 ? v0 : 0) * K * 2);
-    const __amdgpu_buffer_rsrc_t w1 = uniform_rsrc(We + (int64_t)((GATED ? g.up_off : 0) + n1) * K, (int64_t)(v1 > 0 ? v1 : 0) * K * 2);
+    const __amdgpu_buffer_rsrc_t w0 = rows_rsrc(We, n0, v0, K);
+    const __amdgpu_buffer_rsrc_t w1 = rows_rsrc(We, (GATED ? g.up_off : 0) + n1, v1, K);
     const __amdgpu_buffer_rsrc_t xr = uniform_rsrc(g.A, g.a_rows * K * 2);
     const uint32_t rowstep = 8 * (uint32_t)K * 2;
 #pragma unroll
