@@ -60,11 +60,14 @@ def algorithmic_work(cfg, counts: np.ndarray):
 
 
 def kernel_source_sha() -> str:
-    """Hash of the grouped-FFN kernel source: counter summaries taken on
+    """Hash of the grouped-FFN kernel sources: counter summaries taken on
     another version of the kernel no longer describe this one."""
     import hashlib
-    path = os.path.join(ROOT, "paper_2606_26607_amd", "csrc", "ffn.hip")
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()
+    h = hashlib.sha256()
+    for name in ("ffn.hip", "ffn_dev.h", "ffn_stream.h"):
+        with open(os.path.join(ROOT, "paper_2606_26607_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic(workload: str, per: str = "dispatch"):
