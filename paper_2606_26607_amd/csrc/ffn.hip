@@ -2261,7 +2261,8 @@ hipError_t launch_grouped_ffn(const uint16_t *x, int64_t x_rows, const int32_t *
                               int64_t shared_rows, const uint16_t *sw13, const uint16_t *sw2,
                               uint16_t *shared_y, void *ws, hipStream_t s)
 {
-    if (cap + shared_rows == 0) return hipSuccess;
+    // (rows gathered from no tokens: there are none, whatever the capacity)
+    if (cap + shared_rows == 0 || (row_index != nullptr && x_rows == 0)) return hipSuccess;
     const FfnCall c(x_rows, row_index != nullptr, El, cap, H, Is, shared_rows, ws);
     if (shared_rows > 0 && !c.big) return hipErrorNotSupported;  // the host API checks this first
     const FfnKernels which = ffn_kernels(c, x_rows, row_index != nullptr, kdiv);

@@ -13,7 +13,7 @@ import paper_2606_26607_amd as moe
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "libmoe.h")
 OK, INVALID, UNSUPPORTED, WORKSPACE = 0, 1, 2, 3
-FAKE = ctypes.c_void_p(0x100000)  # never dereferenced: every call below fails validation
+FAKE = ctypes.c_void_p(0x100000)  # never dereferenced: every call below fails validation or launches nothing
 
 
 def declared_functions():
@@ -152,6 +152,15 @@ def test_ffn_rejects():
     assert call(xr=32) == INVALID                            # permuted x shorter than cap_rows
     assert call(xr=-1) == INVALID
     assert call(r2p=FAKE, k=0) == INVALID                    # gather without a slot count
+
+
+def test_ffn_of_no_tokens():
+    """A fixed-capacity gathered call with no tokens in this step is a call with no rows: accepted, nothing launched
+    (so it returns without a GPU)."""
+    L = moe.lib()
+    for H, Is in ((4096, 1536), (1000, 200)):
+        need = L.moe_ffn_workspace_size(1024, 16, H, Is)
+        assert L.moe_grouped_ffn(FAKE, 0, FAKE, 8, FAKE, 16, 1024, H, Is, FAKE, FAKE, FAKE, FAKE, need, None) == OK
 
 
 def test_ffn_shared_rejects():

@@ -133,3 +133,21 @@ def test_mid_layer(oracle, T, E, k, I, zipf):
     np.testing.assert_array_equal(got[0][0], got[1][0])
     np.testing.assert_array_equal(got[0][1], got[1][1])
     assert_close_rel(bf16_f64(got[1][1]), oracle.layer(inp), what=f"T={T} E={E} k={k}")
+
+
+@pytest.mark.parametrize("H,Is", [(256, 512), (4096, 1536), (1000, 200)])
+def test_no_tokens(H, Is):
+    """A gathered call of fixed capacity without tokens writes nothing."""
+    El, cap, k = 16, 320, 8
+    x = torch.zeros((1, H), dtype=torch.bfloat16, device="cuda")
+    w13 = torch.zeros((El, 2 * Is, H), dtype=torch.bfloat16, device="cuda")
+    w2 = torch.zeros((El, H, Is), dtype=torch.bfloat16, device="cuda")
+    r2p = torch.zeros(cap, dtype=torch.int32, device="cuda")
+    y = torch.full((cap, H), 7.0, dtype=torch.bfloat16, device="cuda")
+    offs = torch.zeros(El + 1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(moe.ffn_workspace_size(cap, El, H, Is), dtype=torch.uint8, device="cuda")
+    st = moe.lib().moe_grouped_ffn(x.data_ptr(), 0, r2p.data_ptr(), k, offs.data_ptr(), El, cap, H, Is, w13.data_ptr(),
+                                   w2.data_ptr(), y.data_ptr(), ws.data_ptr(), ws.numel(),
+                                   torch.cuda.current_stream().cuda_stream or None)
+    torch.cuda.synchronize()
+    assert st == 0 and bool((y == 7.0).all())
