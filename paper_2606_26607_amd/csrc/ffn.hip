@@ -1978,6 +1978,7 @@ struct FfnCall {
     FfnLayout L;
     int El, ne, H, Is;
     int64_t cap, sc, rows, n_cnt;
+    int64_t pairs;  // most routed rows, by which the kernels and their shapes are chosen
     bool big;
     int32_t *pre, *pre_ld, *pre_s, *pre_sd, *split, *split_d, *cnt;
     int4 *mt_g, *mt_d;
@@ -1985,9 +1986,9 @@ struct FfnCall {
     uint16_t *h, *h_sh;
     SchedShape sh;
     SchedOut so;
-    FfnCall(int64_t x_rows, bool gather, int El_, int64_t cap_, int H_, int Is_, int64_t sc_, void *ws)
+    FfnCall(int64_t x_rows, bool gather, int k, int El_, int64_t cap_, int H_, int Is_, int64_t sc_, void *ws)
         : L(cap_ + sc_, El_ + (sc_ > 0 ? 1 : 0), H_, Is_), El(El_), ne(El_ + (sc_ > 0 ? 1 : 0)), H(H_), Is(Is_),
-          cap(cap_), sc(sc_), rows(cap_ + sc_)
+          cap(cap_), sc(sc_), rows(cap_ + sc_), pairs(gather ? x_rows * (k < El_ ? k : El_) : cap_)
     {
         char *base = static_cast<char *>(ws);
         pre = reinterpret_cast<int32_t *>(base);                     // large class, gate-up
@@ -2015,8 +2016,11 @@ struct FfnCall {
 // those of ffn_stream.h, for few rows per expert (FFN_STREAM) or some dozens
 // (FFN_MID).  The choice is the host's, so it rests on bounds: no expert has
 // more rows than `rows` (the tokens of a gathered call, as no expert takes a
-// token twice; else all rows), and their mean is at most R = cap / El (an EP
-// rank's own mean is lower).  The lines lie where the kernels win whatever the
+// token twice; else all rows), and their mean is at most R = pairs / El (an EP
+// rank's own mean is lower).  A gathered call's bounds come from its tokens
+// and k, never from its capacity: a layer call and its four separate calls then
+// choose alike, and sum in the same order, whatever capacity the caller gives
+// the rows.  The lines lie where the kernels win whatever the
 // load; measured in us, tiled / streaming / mid, balanced and under a Zipf(1.2)
 // load:
 //   at most 64 rows: one expert of H 4096, I 14336 with all 64 117 / 106; 32 + 1
@@ -2052,7 +2056,7 @@ enum FfnKernels { FFN_TILED, FFN_STREAM, FFN_MID };
 FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
 {
     if (!c.big || c.H > (1 << 20) || c.Is > (1 << 20)) return FFN_TILED;
-    const int64_t rows = gather ? x_rows : c.rows, R = ceil_div(c.cap, c.El);
+    const int64_t rows = gather ? x_rows : c.rows, R = ceil_div(c.pairs, c.El);
     if (rows <= 64) return FFN_STREAM;
     if ((int64_t)c.El * 6 * c.H * c.Is <= STREAM_CACHED_BYTES && rows <= 512) return FFN_STREAM;
     if (!ffn_whole_slices(c.H, c.Is)) {
@@ -2075,7 +2079,7 @@ FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
 }
 
 template <bool GATED>
-hipError_t launch_stream(ffn_stream::StreamArgs a, FfnKernels which, int64_t rows, int ne, int kind, hipStream_t s)
+hipError_t launch_stream(ffn_stream::StreamArgs a, FfnKernels which, int64_t rows, int64_t pairs, int ne, int kind, hipStream_t s)
 {
     ffn_stream::LaunchStamps ts{nullptr, nullptr, DEV_TS_SLOTS};
     const int slot = device_ts_slot(kind);
@@ -2086,7 +2090,7 @@ hipError_t launch_stream(ffn_stream::StreamArgs a, FfnKernels which, int64_t row
         ts.start = static_cast<unsigned long long *>(p) + slot;
         ts.end = ts.start + 8 * DEV_TS_SLOTS;
     }
-    const int64_t active = ne < a.cap + a.shared_rows ? ne : a.cap + a.shared_rows, R = ceil_div(a.cap, a.El);
+    const int64_t active = ne < pairs + a.shared_rows ? ne : pairs + a.shared_rows, R = ceil_div(pairs, a.El);
     const int slices = a.K / ffn_stream::SK;
     // Weights that cannot stay in the caches are loaded with the non-temporal
     // hint (64 tokens of the DeepSeek-shaped slice 420 -> 373 us), where the
@@ -2160,12 +2164,12 @@ hipError_t launch_stream_gemms(const FfnCall &c, FfnKernels which, const uint16_
         KernelTimer timer(MOE_K_GATE_UP, s);
         const ffn_stream::StreamArgs a{x, row_index, kdiv, row_index ? x_rows : c.rows, offsets, El, cap, sc, (int)shared_begin, Is, H,
                                        w13, (int64_t)2 * Is * H, sw13, Is, c.h, c.h_sh, 0};
-        if ((err = launch_stream<true>(a, which, rows, c.ne, MOE_K_GATE_UP, s)) != hipSuccess) return err;
+        if ((err = launch_stream<true>(a, which, rows, c.pairs, c.ne, MOE_K_GATE_UP, s)) != hipSuccess) return err;
     }
     KernelTimer timer(MOE_K_DOWN, s);
     const ffn_stream::StreamArgs a{c.h, nullptr, 1, c.rows, offsets, El, cap, sc, (int)shared_begin, H, Is,
                                    w2, (int64_t)H * Is, sw2, 0, y, shared_y, 0};
-    return launch_stream<false>(a, which, rows, c.ne, MOE_K_DOWN, s);
+    return launch_stream<false>(a, which, rows, c.pairs, c.ne, MOE_K_DOWN, s);
 }
 
 // One tiled GEMM launch.  A K that is not whole slices takes kernels of its
@@ -2263,7 +2267,7 @@ hipError_t launch_grouped_ffn(const uint16_t *x, int64_t x_rows, const int32_t *
 {
     // (rows gathered from no tokens: there are none, whatever the capacity)
     if (cap + shared_rows == 0 || (row_index != nullptr && x_rows == 0)) return hipSuccess;
-    const FfnCall c(x_rows, row_index != nullptr, El, cap, H, Is, shared_rows, ws);
+    const FfnCall c(x_rows, row_index != nullptr, kdiv, El, cap, H, Is, shared_rows, ws);
     if (shared_rows > 0 && !c.big) return hipErrorNotSupported;  // the host API checks this first
     const FfnKernels which = ffn_kernels(c, x_rows, row_index != nullptr, kdiv);
     if (which != FFN_TILED)
@@ -2414,7 +2418,7 @@ hipError_t launch_layer(const uint16_t *x, const float *logits, int64_t T, int E
             return err;
         return launch_combine(y, cap, p2r, w, T, k, H, sc > 0 ? shared_y : nullptr, sb, sc, 0, out, s);
     }
-    const FfnCall c(T, true, El, cap, H, Is, sc, ws_ffn);
+    const FfnCall c(T, true, k, El, cap, H, Is, sc, ws_ffn);
     const FfnKernels which = ffn_kernels(c, T, true, k);
     if (which != FFN_TILED) {
         // these GEMMs take no tile schedule: the permutation is all the

@@ -151,3 +151,26 @@ def test_no_tokens(H, Is):
                                    torch.cuda.current_stream().cuda_stream or None)
     torch.cuda.synchronize()
     assert st == 0 and bool((y == 7.0).all())
+
+
+@pytest.mark.parametrize("T,E,k,e0,El,H,Is", [
+    (400, 128, 8, 16, 16, 2048, 768),   # by capacities: few rows per expert or many
+    (2, 64, 8, 0, 8, 256, 3072),        # ... two waves on a strip's K or one
+    (300, 64, 4, 0, 16, 1000, 328)])
+def test_capacity_leaves_bits_alone(oracle, T, E, k, e0, El, H, Is):
+    """The rows' capacity is a buffer size: gathered calls of the same tokens write the same bits under each."""
+    ids = mi.random_topk_ids(T, E, k, seed=T)
+    _, offs, r2p, _ = oracle.permute(ids, e0, El)
+    n, most = int(offs[-1]), T * min(k, El)
+    x = dev_bf16(mi.random_bf16((T, H), seed=T, tag=95))
+    w13 = dev_bf16(mi.random_bf16((El, 2 * Is, H), seed=1, tag=96, std=0.03))
+    w2 = dev_bf16(mi.random_bf16((El, H, Is), seed=1, tag=97, std=0.03))
+    got = []
+    for cap in (n, most, 3 * most):
+        full = torch.full((cap,), -1, dtype=torch.int32)
+        full[:n] = torch.from_numpy(r2p[:n])
+        y = moe.grouped_ffn(x, torch.from_numpy(offs).cuda(), w13, w2, row_to_pair=full.cuda(), k=k, cap_rows=cap)
+        torch.cuda.synchronize()
+        got.append(host_bf16(y)[:n])
+    np.testing.assert_array_equal(got[0], got[1])
+    np.testing.assert_array_equal(got[1], got[2])
