@@ -2020,62 +2020,75 @@ struct FfnCall {
 // rank's own mean is lower).  A gathered call's bounds come from its tokens
 // and k, never from its capacity: a layer call and its four separate calls then
 // choose alike, and sum in the same order, whatever capacity the caller gives
-// the rows.  The lines lie where the kernels win whatever the
-// load; measured in us, tiled / streaming / mid, balanced and under a Zipf(1.2)
-// load:
-//   at most 64 rows: one expert of H 4096, I 14336 with all 64 117 / 106; 32 + 1
-//     experts of H 7168, I 2048 398 / 370;
-//   up to 320 tokens, mean at most 64 (48 for fewer than 8 experts): 128 slices
-//     of H 4096, I 192, 300 tokens 165 / 134 / 159 and 172 / 134 / 140; 32 experts of
-//     H 7168, I 2048, 200 tokens 485 / 453 and 198 / 161 (4 of H 4096, I 14336, mean at
-//     most 100: 272 / 278 and 395 / 430);
-//   up to 512 tokens, mean at most 24: 256 slices of a DeepSeek-shaped layer;
-//     past that mean the mid kernel: 128 experts of H 2048, I 384, mean 31, 155 / 151 /
-//     142 and 140 / 163 / 144;
-//   top-1 and top-2 layers of 8 experts and more up to 512 tokens, mean 48 to
-//     128: 8 experts of H 4096, I 1792, 300 tokens 146 / 146 / 95 and 164 / 148 / 147;
-//   rows not gathered, whole-slice widths: mean at most 28 streaming (16
-//     experts of H 4096, I 1536, 400 rows 126 / 108 / 118 and 146 / 136 / 149), 64 to
-//     112 mid for 8 experts and more (1500 rows 207 / 241 / 155 and 186 / 248 / 191);
-//   widths that are not whole slices, where the tiled kernels' rows straddle
-//     lines: mean at most 48 streaming, to 96 mid, to 256 where an expert's
-//     weights are a few MB (12 experts of H 1000, I 1200, 800 rows 58 / 42 / 38,
-//     2500 rows 82 / 93 / 57; 128 slices of H 2048, I 96, 2051 tokens 143 / - / 121;
-//     but 96 of H 3608, I 480, 1656 tokens, mean 138, 423 / - / 527); up to 2 MB
-//     and 3072 tokens mid at any mean (12 slices of H 1000, I 200, 2500 tokens
-//     83 / 87 / 64, Zipf 83 / 107 / 88, 98 in the general kernel, 935 tokens
-//     79 / 49 / 43 and 74 / 55 / 52; 10 of H 328, I 808, 2500 tokens 72 / 73 / 51
-//     and 77 / 84 / 63);
-//   weights of a few MB, which stay in the caches: up to 512 rows streaming
-//     (8 experts of H 256, I 512, 512 tokens 56 / 36).
-// Past these a hot expert's rows are better off in 256-row tiles (128 slices
-// of H 4096, I 192, 1000 tokens: 250 / 227 / 188 balanced, but 207 / 288 / 236).
-constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20, RAGGED_SMALL_BYTES = (int64_t)8 << 20,
+// the rows.
+//
+// What decides is the experts' loads, which only the device knows: rows of
+// one hot expert are better off in 256-row tiles (1 PF and more; the mid
+// kernel does 0.5, the streaming one re-reads the expert's weights every 64
+// rows).  The lines therefore lie where the kernels win under an even load
+// and lose nothing that shows under Zipf(0.7), Zipf(1.2) and half of all rows
+// on one expert, over some 60 layer and FFN shapes of 1 to 256 experts.
+// Measured in us, tiled / chosen, evenly loaded and under Zipf(1.2):
+//   at most 64 rows: one expert of H 4096, I 14336, 48 tokens 101 / 73 and 114 /
+//     74; 256 slices of H 7168, I 512, 16 tokens 393 / 366 and 138 / 122, but 64
+//     tokens 777 / 759 and 230 / 242;
+//   weights of a few MB, which stay in the caches, up to 512 rows (8 experts
+//     of H 256, I 512, 512 tokens 56 / 36);
+//   experts of up to 10 MB: gathered, up to 448 tokens with a mean of at most
+//     28 and up to 256 with one of 64 (128 slices of H 4096, I 192, 320 tokens
+//     167 / 136 and 171 / 138; 64 of H 2048, I 768, 256 tokens 132 / 123 and 110 /
+//     111; at 512 138 / 150 and 124 / 161); else up to 768 rows (24 experts of
+//     H 2048, I 768 63 / 54 and 76 / 69; 64 of them, 1536 rows, half of them one
+//     expert's, 138 / 156);
+//   larger experts: gathered, up to 32 experts, 192 tokens and a mean of 40
+//     (48 for fewer than 8 experts), where H is at most 4.5 I (a hot expert's
+//     passes only spread over its I / 16 strips: 128 slices of H 4096, I 768,
+//     128 tokens 433 / 405, but 230 / 269); 32 experts of H 7168, I 2048, 160 tokens
+//     486 / 467 and 165 / 150; else up to 256 rows with a mean of 28 (16 of H
+//     4096, I 1536, 256 rows 117 / 101 and 125 / 124; 320 rows of 40 of H 5120, I
+//     1536 320 / 311, but 314 / 329);
+//   top-1 and top-2 layers, mean 88 to 112, up to 512 tokens, mid (8 slices of H
+//     4096, I 2048, 400 tokens 171 / 109 and 171 / 166; below that mean 8 of H 4096,
+//     I 896, 320 tokens 83 / 76, but 76 / 85 under Zipf(0.7); what it costs: an EP
+//     slice, 8 of 32 experts of H 5120, I 1536, 94 / 88, but 94 / 105).
+// On many rows not gathered nothing but the tiles is safe: the mid kernel
+// takes 155 instead of 245 us for 128 experts of H 2048, I 384, 66 rows each, but
+// 239 instead of 184 under the Zipf load, and 403 instead of 105 if one expert
+// holds all of 14208 rows.
+// Widths that are not whole slices, where the tiled kernels' rows straddle
+// lines: mean at most 48 streaming, to 96 mid, to 256 where an expert's
+//   weights are a few MB (12 experts of H 1000, I 1200, 800 rows 58 / 42 / 38,
+//   2500 rows 82 / 93 / 57; 128 slices of H 2048, I 96, 2051 tokens 143 / - / 121;
+//   but 96 of H 3608, I 480, 1656 tokens, mean 138, 423 / - / 527); up to 2 MB
+//   and 3072 tokens mid at any mean (12 slices of H 1000, I 200, 2500 tokens
+//   83 / 87 / 64, Zipf 83 / 107 / 88, 98 in the general kernel, 935 tokens
+//   79 / 49 / 43 and 74 / 55 / 52; 10 of H 328, I 808, 2500 tokens 72 / 73 / 51
+//   and 77 / 84 / 63).
+constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20, SMALL_EXPERT_BYTES = (int64_t)10 << 20,
+                  MID_EXPERT_BYTES = (int64_t)48 << 20, RAGGED_SMALL_BYTES = (int64_t)8 << 20,
                   RAGGED_MID_BYTES = (int64_t)2 << 20, RAGGED_MID_ROWS = 3072;
 enum FfnKernels { FFN_TILED, FFN_STREAM, FFN_MID };
 FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
 {
     if (!c.big || c.H > (1 << 20) || c.Is > (1 << 20)) return FFN_TILED;
     const int64_t rows = gather ? x_rows : c.rows, R = ceil_div(c.pairs, c.El);
+    const int64_t bytes = (int64_t)6 * c.H * c.Is;  // an expert's weights
     if (rows <= 64) return FFN_STREAM;
-    if ((int64_t)c.El * 6 * c.H * c.Is <= STREAM_CACHED_BYTES && rows <= 512) return FFN_STREAM;
+    if (c.El * bytes <= STREAM_CACHED_BYTES && rows <= 512) return FFN_STREAM;
     if (!ffn_whole_slices(c.H, c.Is)) {
-        const int64_t bytes = (int64_t)6 * c.H * c.Is;  // an expert's weights
         if (rows <= RAGGED_MID_ROWS && bytes <= RAGGED_MID_BYTES) return R <= 48 ? FFN_STREAM : FFN_MID;
         if (rows > 4096 || R > (bytes <= RAGGED_SMALL_BYTES ? 256 : 96)) return FFN_TILED;
         return R <= 48 ? FFN_STREAM : FFN_MID;
     }
+    const bool small = bytes <= SMALL_EXPERT_BYTES, wide = (int64_t)2 * c.H < (int64_t)9 * c.Is;
     if (!gather) {
-        if (R <= 28 && rows <= 1536) return FFN_STREAM;
-        return R >= 64 && R <= 112 && c.El >= 8 ? FFN_MID : FFN_TILED;
+        if (small) return rows <= 768 ? FFN_STREAM : FFN_TILED;
+        return rows <= 256 && R <= 28 && c.El <= 64 && wide ? FFN_STREAM : FFN_TILED;
     }
-    if (rows <= 320 && R <= (c.El < 8 ? 48 : 64)) {
-        if (k <= 2 && c.El >= 8 && rows > 128 && R > 48) return FFN_MID;
+    if (c.El < 8) return R <= 48 ? FFN_STREAM : FFN_TILED;
+    if (small ? (rows <= 448 && R <= 28) || (rows <= 256 && R <= 64) : rows <= 192 && R <= 40 && c.El <= 32 && wide)
         return FFN_STREAM;
-    }
-    if (rows > 512) return FFN_TILED;
-    if (R <= 24) return FFN_STREAM;
-    return R <= 32 || (k <= 2 && c.El >= 8 && R <= 128) ? FFN_MID : FFN_TILED;
+    return k <= 2 && bytes <= MID_EXPERT_BYTES && rows <= 512 && R >= 88 && R <= 112 ? FFN_MID : FFN_TILED;
 }
 
 template <bool GATED>

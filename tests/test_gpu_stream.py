@@ -6,7 +6,7 @@ import torch
 
 import moe_inputs as mi
 import paper_2606_26607_amd as moe
-from tests.util import assert_close_rel, bf16_f64, dev_bf16, host_bf16
+from tests.util import assert_close_rel, bf16_f64, dev_bf16, host_bf16, launches_tiles
 
 pytestmark = pytest.mark.gpu
 
@@ -48,20 +48,20 @@ def test_stream_edges(oracle, rows, gather, H, Is):
     runs = []
     for _ in range(2):
         y = torch.full((n + 1, H), 7.0, dtype=torch.bfloat16, device="cuda")
-        moe.grouped_ffn(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), y=y, cap_rows=n,
-                        row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1)
-        torch.cuda.synchronize()
+        assert not launches_tiles(lambda: moe.grouped_ffn(
+            dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), y=y, cap_rows=n,
+            row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1))
         runs.append(host_bf16(y))
     np.testing.assert_array_equal(runs[0], runs[1])
     assert np.all(bf16_f64(runs[0])[n] == 7.0)  # nothing past the rows
     assert_close_rel(bf16_f64(runs[0])[:n], want, what=f"rows={rows} H={H} Is={Is}")
 
 
-@pytest.mark.parametrize("T", [5, 40, 128])
-def test_stream_shared_and_non_temporal(oracle, T):
+@pytest.mark.parametrize("T,k,tiles", [(5, 4, False), (40, 4, False), (64, 4, False), (128, 4, True), (400, 2, False)])
+def test_stream_shared_and_non_temporal(oracle, T, k, tiles):
     """Weights of more than 64 MiB (loaded with the non-temporal hint), a shared expert beside the routed ones, and
-    every row-block width."""
-    El, E, k, H, Is = 8, 16, 4, 2048, 1088
+    every row-block width; the last through the mid kernel."""
+    El, E, H, Is = 8, 16, 2048, 1088
     ids = mi.random_topk_ids(T, E, k, seed=T)
     _, offs, r2p, _ = oracle.permute(ids, 4, El)
     n, sb, sc = int(offs[-1]), T // 3, T // 2
@@ -73,8 +73,10 @@ def test_stream_shared_and_non_temporal(oracle, T):
     cap = T * k
     full = torch.full((cap,), -1, dtype=torch.int32)
     full[:n] = torch.from_numpy(r2p)
-    y, sy = moe.grouped_ffn_shared(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2),
-                                   full.cuda(), k, cap, sb, sc, dev_bf16(sw13), dev_bf16(sw2))
+    args = (dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), full.cuda(), k, cap, sb, sc,
+            dev_bf16(sw13), dev_bf16(sw2))
+    assert launches_tiles(lambda: moe.grouped_ffn_shared(*args)) == tiles
+    y, sy = moe.grouped_ffn_shared(*args)
     torch.cuda.synchronize()
     assert_close_rel(bf16_f64(host_bf16(y))[:n], oracle.grouped_ffn(x[r2p // k], offs, w13, w2), what="routed")
     assert_close_rel(bf16_f64(host_bf16(sy))[:sc],
@@ -87,8 +89,9 @@ MID = [128, 65, 0, 64, 200, 33, 1, 130]
 
 
 @pytest.mark.parametrize("rows,gather,H,Is", [
-    (MID, False, 128, 128),             # two whole slices: fewer than the loads kept in flight
-    (MID, False, 448, 320), (MID, False, 1024, 192),
+    (MID, False, 128, 128), (MID, False, 448, 320), (MID, False, 1024, 192),  # (streaming)
+    (MID, True, 128, 2752), (MID, True, 2752, 128),  # two whole slices: fewer than the loads kept in flight
+    (MID, True, 1024, 448),
     (MID, False, 200, 72), (MID, False, 56, 264),    # partial last slices; strips past the columns
     (MID, True, 1000, 328),
     ([900, 70, 130, 20], False, 136, 200),
@@ -96,7 +99,8 @@ MID = [128, 65, 0, 64, 200, 33, 1, 130]
 def test_mid_edges(oracle, rows, gather, H, Is):
     El, k, n = len(rows), 2, sum(rows)
     offs = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
-    T = 700 if gather else n
+    # (gathered whole-slice widths: the mean of a top-2 layer is 100)
+    T = n if not gather else 400 if H % 64 == 0 and Is % 64 == 0 else 700
     x = mi.random_bf16((T, H), seed=H + Is, tag=90)
     w13 = mi.random_bf16((El, 2 * Is, H), seed=H, tag=91, std=0.05)
     w2 = mi.random_bf16((El, H, Is), seed=H, tag=92, std=0.05)
@@ -105,16 +109,17 @@ def test_mid_edges(oracle, rows, gather, H, Is):
     runs = []
     for _ in range(2):
         y = torch.full((n + 1, H), 7.0, dtype=torch.bfloat16, device="cuda")
-        moe.grouped_ffn(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), y=y, cap_rows=n,
-                        row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1)
-        torch.cuda.synchronize()
+        assert not launches_tiles(lambda: moe.grouped_ffn(
+            dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), y=y, cap_rows=n,
+            row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1))
         runs.append(host_bf16(y))
     np.testing.assert_array_equal(runs[0], runs[1])
     assert np.all(bf16_f64(runs[0])[n] == 7.0)  # nothing past the rows
     assert_close_rel(bf16_f64(runs[0])[:n], want, what=f"rows={rows} H={H} Is={Is}")
 
 
-@pytest.mark.parametrize("T,E,k,I,zipf", [(300, 8, 2, 4096, None), (480, 8, 1, 4096, 1.2), (400, 100, 8, 520, 1.2)])
+@pytest.mark.parametrize("T,E,k,I,zipf", [(300, 8, 2, 4096, None), (480, 8, 1, 4096, 1.2), (400, 100, 8, 520, 1.2),
+                                           (400, 8, 2, 4096, None), (440, 8, 2, 4096, 1.2)])
 def test_mid_layer(oracle, T, E, k, I, zipf):
     """A layer call and its four separate calls through the mid kernel (with the non-temporal hint in the first), bit
     for bit and against the oracle."""
@@ -174,3 +179,25 @@ def test_capacity_leaves_bits_alone(oracle, T, E, k, e0, El, H, Is):
         got.append(host_bf16(y)[:n])
     np.testing.assert_array_equal(got[0], got[1])
     np.testing.assert_array_equal(got[1], got[2])
+
+
+@pytest.mark.parametrize("El,H,Is,rows,k,tiles", [
+    # rows not gathered (k = 0): few, or all of them too many for a host that cannot see a hot expert
+    (16, 1024, 512, 768, 0, False), (16, 1024, 512, 769, 0, True), (16, 1024, 512, 1500, 0, True),
+    (16, 2048, 1024, 256, 0, False), (16, 2048, 1024, 257, 0, True), (16, 5120, 1024, 200, 0, True),
+    (72, 1536, 1280, 100, 0, True),
+    # gathered: rows is the tokens
+    (32, 7168, 256, 64, 8, False), (32, 7168, 256, 65, 8, True), (33, 2048, 1024, 100, 2, True),
+    (16, 2048, 1024, 160, 4, False), (16, 2048, 1024, 161, 4, True), (4, 2048, 1024, 96, 2, False),
+    (4, 2048, 1024, 97, 2, True), (8, 2048, 768, 256, 2, False), (8, 2048, 768, 257, 2, True),
+    (16, 2048, 512, 448, 1, False), (16, 2048, 512, 449, 1, True),
+    (8, 2048, 1024, 348, 2, True), (8, 2048, 1024, 352, 2, False), (8, 2048, 1024, 448, 2, False),
+    (8, 2048, 1024, 449, 2, True), (8, 2048, 1024, 400, 3, True)])
+def test_lines(El, H, Is, rows, k, tiles):
+    """Which whole-slice calls of weights past the caches leave the tiled kernels."""
+    w13 = torch.zeros((El, 2 * Is, H), dtype=torch.bfloat16, device="cuda")
+    w2 = torch.zeros((El, H, Is), dtype=torch.bfloat16, device="cuda")
+    x = torch.zeros((rows, H), dtype=torch.bfloat16, device="cuda")
+    offs = torch.zeros(El + 1, dtype=torch.int32, device="cuda")
+    r2p = torch.zeros(rows * min(k, El), dtype=torch.int32, device="cuda") if k else None
+    assert launches_tiles(lambda: moe.grouped_ffn(x, offs, w13, w2, row_to_pair=r2p, k=max(k, 1))) == tiles

@@ -25,3 +25,22 @@ def assert_close_rel(got: np.ndarray, ref: np.ndarray, rtol: float = OUT_RTOL, w
     assert np.all(np.isfinite(got)), f"{what}: non-finite output"
     assert err <= rtol * scale + 1e-30, f"{what}: max|err|={err:.3e} > {rtol}*max|ref|={rtol * scale:.3e}"
     return err, scale
+
+
+def launched(fn) -> dict:
+    """The kernel kinds that fn's calls launch, with their counts."""
+    import paper_2606_26607_amd as moe
+    from paper_2606_26607_amd.binding import KERNEL_KINDS
+    moe.timing_reset()
+    moe.timing_enable(True)
+    try:
+        fn()
+        torch.cuda.synchronize()
+    finally:
+        moe.timing_enable(False)
+    return {k: n for k in KERNEL_KINDS for n in [moe.timing_read(k)[1]] if n}
+
+
+def launches_tiles(fn) -> bool:
+    """Whether a grouped-FFN call runs the tiled kernels (they take a tile schedule; the streaming ones take none)."""
+    return "schedule" in launched(fn)
