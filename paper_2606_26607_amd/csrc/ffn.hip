@@ -1963,13 +1963,17 @@ namespace {
 
 // Many rows of experts with a few hundred KB of weights, in widths that are
 // not whole slices: most of a 256-wide tile would be padding, and the general
-// kernel's 64x64 tiles take less (us, tiled / general, balanced and under a
-// Zipf(1.2) load, 6000 tokens: 16 experts of H 208, I 32 60 / 50 and 62 / 50, 8 of
-// H 72, I 40 48 / 32 and 49 / 35, 64 of H 520, I 72 87 / 86 and 90 / 84; but 12 of
-// H 1000, I 200, 1.2 MB, 98 / 170).  Up to 4096 rows ffn_kernels chooses.
-bool ffn_narrow(int64_t rows, int H, int Is)
+// kernel's 64x64 tiles take less (us, tiled / general, evenly loaded and under a
+// Zipf(1.2) load: 2 experts of H 208, I 32, 4096 rows 30 / 17 and 33 / 17, top-8 over
+// 16 of them, 6000 tokens 63 / 51 and 62 / 51; 8 of H 72, I 40, 9000 rows 32 / 15 and
+// 32 / 15; 64 of H 520, I 72, 9000 rows 41 / 47 and 52 / 45; but 12 of H 1000, I 200,
+// 1.2 MB, 53 / 75).  Up to 4096 rows with a mean of at most 256, and up to 3072
+// with any, ffn_kernels takes the streaming ones.
+constexpr int64_t NARROW_BYTES = (int64_t)256 << 10;
+bool ffn_narrow(int64_t rows, int64_t R, int H, int Is)
 {
-    return !ffn_whole_slices(H, Is) && rows > 4096 && (int64_t)6 * H * Is <= (int64_t)256 << 10;
+    return !ffn_whole_slices(H, Is) && (int64_t)6 * H * Is <= NARROW_BYTES &&
+           (rows > 4096 || (rows > 3072 && R > 256));
 }
 
 // One grouped-FFN call: its row space (the routed rows [0, cap), then the
@@ -2004,7 +2008,8 @@ struct FfnCall {
         part = reinterpret_cast<float *>(base + L.off_part);
         h = reinterpret_cast<uint16_t *>(base + L.off_h);
         h_sh = h + cap * Is;  // the shared expert's h rows
-        big = ffn_large_tiles(gather ? x_rows : rows, rows, H, Is) && !ffn_narrow(gather ? x_rows : rows, H, Is);
+        big = ffn_large_tiles(gather ? x_rows : rows, rows, H, Is) &&
+              !ffn_narrow(gather ? x_rows : rows, ceil_div(pairs, El), H, Is);
         n_cnt = big ? L.t_gu + L.t_dn + L.ts_gu + L.ts_dn : 0;
         sh = sched_shape(H, Is, L.grid);
         so = SchedOut{{pre, pre_ld}, {pre_s, pre_sd}, {split, split_d}, {mt_g, mt_d}};
@@ -2056,17 +2061,17 @@ struct FfnCall {
 // 239 instead of 184 under the Zipf load, and 403 instead of 105 if one expert
 // holds all of 14208 rows.
 // Widths that are not whole slices, where the tiled kernels' rows straddle
-// lines: mean at most 48 streaming, to 96 mid, to 256 where an expert's
-//   weights are a few MB (12 experts of H 1000, I 1200, 800 rows 58 / 42 / 38,
-//   2500 rows 82 / 93 / 57; 128 slices of H 2048, I 96, 2051 tokens 143 / - / 121;
-//   but 96 of H 3608, I 480, 1656 tokens, mean 138, 423 / - / 527); up to 2 MB
-//   and 3072 tokens mid at any mean (12 slices of H 1000, I 200, 2500 tokens
-//   83 / 87 / 64, Zipf 83 / 107 / 88, 98 in the general kernel, 935 tokens
-//   79 / 49 / 43 and 74 / 55 / 52; 10 of H 328, I 808, 2500 tokens 72 / 73 / 51
-//   and 77 / 84 / 63).
+// lines (tiled / streaming / mid): up to 4096 rows mid where an expert's weights
+// are up to 2 MB and all rows at most 20000 (4 experts of H 328, I 808, 4096 rows
+// 50 / 42 / 30 and 60 / 55 / 43; 128 slices of H 2048, I 96, top-8, 3000 tokens
+// 138 / 178 / 150, but 154 / 296 / 244), or the mean at most
+// 256 (up to 8 MB) or 96 (12 of H 1000, I 1200, 800 rows 58 / 42 / 38; 96 of H 3608,
+// I 480, 1656 tokens, mean 138, 423 / - / 527); streaming up to a mean of 48 and
+// 3072 rows (128 of H 2048, I 96, 2100 rows 58 / 40 / 50 and 97 / 54 / 77; 4096 rows,
+// half of them one expert's, 100 / 125 / 96).
 constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20, SMALL_EXPERT_BYTES = (int64_t)10 << 20,
                   MID_EXPERT_BYTES = (int64_t)48 << 20, RAGGED_SMALL_BYTES = (int64_t)8 << 20,
-                  RAGGED_MID_BYTES = (int64_t)2 << 20, RAGGED_MID_ROWS = 3072;
+                  RAGGED_MID_BYTES = (int64_t)2 << 20, RAGGED_MID_PAIRS = 20000;
 enum FfnKernels { FFN_TILED, FFN_STREAM, FFN_MID };
 FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
 {
@@ -2076,9 +2081,11 @@ FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
     if (rows <= 64) return FFN_STREAM;
     if (c.El * bytes <= STREAM_CACHED_BYTES && rows <= 512) return FFN_STREAM;
     if (!ffn_whole_slices(c.H, c.Is)) {
-        if (rows <= RAGGED_MID_ROWS && bytes <= RAGGED_MID_BYTES) return R <= 48 ? FFN_STREAM : FFN_MID;
-        if (rows > 4096 || R > (bytes <= RAGGED_SMALL_BYTES ? 256 : 96)) return FFN_TILED;
-        return R <= 48 ? FFN_STREAM : FFN_MID;
+        if (rows > 4096) return FFN_TILED;
+        if (bytes > NARROW_BYTES && (bytes <= RAGGED_MID_BYTES ? c.pairs > RAGGED_MID_PAIRS
+                                                               : R > (bytes <= RAGGED_SMALL_BYTES ? 256 : 96)))
+            return FFN_TILED;
+        return R <= 48 && rows <= 3072 ? FFN_STREAM : FFN_MID;
     }
     const bool small = bytes <= SMALL_EXPERT_BYTES, wide = (int64_t)2 * c.H < (int64_t)9 * c.Is;
     if (!gather) {

@@ -6,7 +6,7 @@ import torch
 
 import moe_inputs as mi
 import paper_2606_26607_amd as moe
-from tests.util import assert_close_rel, bf16_f64, dev_bf16, host_bf16, launches_tiles
+from tests.util import assert_close_rel, bf16_f64, dev_bf16, host_bf16, ffn_route
 
 pytestmark = pytest.mark.gpu
 
@@ -48,7 +48,7 @@ def test_stream_edges(oracle, rows, gather, H, Is):
     runs = []
     for _ in range(2):
         y = torch.full((n + 1, H), 7.0, dtype=torch.bfloat16, device="cuda")
-        assert not launches_tiles(lambda: moe.grouped_ffn(
+        assert "streaming" == ffn_route(lambda: moe.grouped_ffn(
             dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), y=y, cap_rows=n,
             row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1))
         runs.append(host_bf16(y))
@@ -75,7 +75,7 @@ def test_stream_shared_and_non_temporal(oracle, T, k, tiles):
     full[:n] = torch.from_numpy(r2p)
     args = (dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), full.cuda(), k, cap, sb, sc,
             dev_bf16(sw13), dev_bf16(sw2))
-    assert launches_tiles(lambda: moe.grouped_ffn_shared(*args)) == tiles
+    assert ffn_route(lambda: moe.grouped_ffn_shared(*args)) == ("tiled" if tiles else "streaming")
     y, sy = moe.grouped_ffn_shared(*args)
     torch.cuda.synchronize()
     assert_close_rel(bf16_f64(host_bf16(y))[:n], oracle.grouped_ffn(x[r2p // k], offs, w13, w2), what="routed")
@@ -109,7 +109,7 @@ def test_mid_edges(oracle, rows, gather, H, Is):
     runs = []
     for _ in range(2):
         y = torch.full((n + 1, H), 7.0, dtype=torch.bfloat16, device="cuda")
-        assert not launches_tiles(lambda: moe.grouped_ffn(
+        assert "streaming" == ffn_route(lambda: moe.grouped_ffn(
             dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), y=y, cap_rows=n,
             row_to_pair=None if r2p is None else torch.from_numpy(r2p).cuda(), k=k if gather else 1))
         runs.append(host_bf16(y))
@@ -192,12 +192,28 @@ def test_capacity_leaves_bits_alone(oracle, T, E, k, e0, El, H, Is):
     (4, 2048, 1024, 97, 2, True), (8, 2048, 768, 256, 2, False), (8, 2048, 768, 257, 2, True),
     (16, 2048, 512, 448, 1, False), (16, 2048, 512, 449, 1, True),
     (8, 2048, 1024, 348, 2, True), (8, 2048, 1024, 352, 2, False), (8, 2048, 1024, 448, 2, False),
-    (8, 2048, 1024, 449, 2, True), (8, 2048, 1024, 400, 3, True)])
+    (8, 2048, 1024, 449, 2, True), (8, 2048, 1024, 400, 3, True),
+    # widths that are not whole slices
+    (8, 1000, 1208, 2048, 0, False), (8, 1000, 1208, 2049, 0, True), (4, 4096, 360, 384, 0, False),
+    (4, 4096, 360, 385, 0, True), (4, 328, 808, 4096, 0, False), (4, 328, 808, 4097, 0, True),
+    (128, 2048, 96, 2500, 8, False), (128, 2048, 96, 2501, 8, True)])
 def test_lines(El, H, Is, rows, k, tiles):
-    """Which whole-slice calls of weights past the caches leave the tiled kernels."""
+    """Which calls of weights past the caches leave the tiled kernels."""
+    assert zeros_route(El, H, Is, rows, k) == ("tiled" if tiles else "streaming")
+
+
+@pytest.mark.parametrize("El,H,Is,rows,k,general", [
+    (2, 208, 32, 3072, 0, False), (2, 208, 32, 3073, 0, True), (16, 208, 32, 4096, 0, False),
+    (16, 208, 32, 4097, 0, True), (8, 72, 40, 3072, 2, False), (8, 72, 40, 3073, 2, True)])
+def test_narrow_lines(El, H, Is, rows, k, general):
+    """Which calls of narrow experts run the general kernel (none runs the tiled ones)."""
+    assert zeros_route(El, H, Is, rows, k) == ("general" if general else "streaming")
+
+
+def zeros_route(El, H, Is, rows, k):
     w13 = torch.zeros((El, 2 * Is, H), dtype=torch.bfloat16, device="cuda")
     w2 = torch.zeros((El, H, Is), dtype=torch.bfloat16, device="cuda")
     x = torch.zeros((rows, H), dtype=torch.bfloat16, device="cuda")
     offs = torch.zeros(El + 1, dtype=torch.int32, device="cuda")
     r2p = torch.zeros(rows * min(k, El), dtype=torch.int32, device="cuda") if k else None
-    assert launches_tiles(lambda: moe.grouped_ffn(x, offs, w13, w2, row_to_pair=r2p, k=max(k, 1))) == tiles
+    return ffn_route(lambda: moe.grouped_ffn(x, offs, w13, w2, row_to_pair=r2p, k=max(k, 1)))

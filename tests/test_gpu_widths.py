@@ -48,9 +48,10 @@ def test_partial_last_slice(oracle, H, Is, gather):
 
 @pytest.mark.parametrize("H,Is,rows", [
     (208, 32, [2500, 0, 300, 1]),                        # mid kernel, more 128-row runs than its grid holds
-    (1000, 328, [3000, 72]), (1000, 328, [3000, 73]),    # either side of its rows: mid, tiled
+    (1000, 328, [3000, 72]), (1000, 328, [3000, 73]),
+    (1000, 328, [4000, 96]), (1000, 328, [4000, 97]),    # either side of its rows: mid, tiled
     (1000, 352, [500, 300]),                             # weights just above its size: tiled
-    (208, 32, [4000, 96]), (208, 32, [4000, 97]),        # tiled; the general kernel past it
+    (208, 32, [4000, 96]), (208, 32, [4000, 97]),        # the general kernel
     (72, 40, [4100, 0, 5]), (8, 8, [5000])])
 def test_small_weights_many_rows(oracle, H, Is, rows):
     n = sum(rows)

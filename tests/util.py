@@ -41,6 +41,20 @@ def launched(fn) -> dict:
     return {k: n for k in KERNEL_KINDS for n in [moe.timing_read(k)[1]] if n}
 
 
-def launches_tiles(fn) -> bool:
-    """Whether a grouped-FFN call runs the tiled kernels (they take a tile schedule; the streaming ones take none)."""
-    return "schedule" in launched(fn)
+def ffn_route(fn) -> str:
+    """Which kernels run a grouped-FFN call: "streaming" (they take no tile schedule), "tiled", or "general" (the only
+    ones that take no device timestamps)."""
+    import paper_2606_26607_amd as moe
+    if "schedule" not in launched(fn):
+        return "streaming"
+    moe.timing_device_clear()
+    moe.timing_device_reset()
+    moe.timing_device_enable(True)
+    try:
+        fn()
+        torch.cuda.synchronize()
+        n = moe.timing_device_read("gate_up")[1]
+    finally:
+        moe.timing_device_enable(False)
+        moe.timing_device_clear()
+    return "tiled" if n else "general"
