@@ -162,6 +162,11 @@ moe_status moe_permute_noalloc(const int32_t *topk_ids, int64_t T, int k, int E,
  * 256-byte aligned (holds the bf16 intermediate h, the tile schedule and the
  * split-K partials; its size depends on the current device's compute unit
  * count, which the query reads with hipGetDevice / hipDeviceGetAttribute).
+ * Ask the library at hand: the size is not part of the interface.  At 256
+ * compute units the partials take up to 64 MiB, and 128 MiB more where H or
+ * I_s is above 8128; widths that are not multiples of 64 (or below 128) hold
+ * them as others do, unless an expert's weights are at most 256 KiB (none).
+ * Calls in stream order may share one workspace.
  */
 size_t moe_ffn_workspace_size(int64_t cap_rows, int n_local_experts, int H, int I_s);
 moe_status moe_grouped_ffn(const uint16_t *x, int64_t x_rows, const int32_t *row_to_pair, int k,

@@ -579,8 +579,6 @@ class MoeLayer:
         }
         self.ws_perm = torch.empty(max(permute_workspace_size(T, k, self.El), 256), dtype=torch.uint8,
                                    device=dev)
-        self.ws_ffn = torch.empty(ffn_workspace_size(cap1, self.El, self.H, self.I_s), dtype=torch.uint8,
-                                  device=dev)
         self.y = torch.empty((cap1, self.H), dtype=torch.bfloat16, device=dev)
         self.out = torch.empty((T, self.H), dtype=torch.bfloat16, device=dev)
         self.sw13, self.sw2 = sw13, sw2
@@ -596,8 +594,6 @@ class MoeLayer:
                                  and self.H >= 128 and self.I_s >= 128)
             if self.fused_shared:
                 self.sw13_2d, self.sw2_2d = sw13.reshape(2 * sIs, self.H), sw2.reshape(self.H, sIs)
-                self.ws_ffn = torch.empty(ffn_workspace_size(cap1 + self.sc, self.El + 1, self.H, self.I_s),
-                                          dtype=torch.uint8, device=dev)
             else:
                 self.s_offsets = torch.tensor([0, self.sc], dtype=torch.int32, device=dev)
                 self.ws_sh = torch.empty(ffn_workspace_size(self.sc, 1, self.H, sIs), dtype=torch.uint8,
@@ -609,8 +605,14 @@ class MoeLayer:
         if self.one_call:
             self.ws_layer = torch.empty(max(layer_workspace_size(T, k, self.El, self.H, self.I_s, self.sc), 256),
                                         dtype=torch.uint8, device=dev)
+            # the four calls' grouped FFN takes the part that the one call
+            # gives it, after the permutation's
+            self.ws_ffn = self.ws_layer[permute_workspace_size(T, k, self.El):]
             if self.sc == 0:
                 self.s_y = None
+        else:
+            self.ws_ffn = torch.empty(ffn_workspace_size(self.cap, self.El, self.H, self.I_s), dtype=torch.uint8,
+                                      device=dev)
 
     def forward(self, x: torch.Tensor, logits: torch.Tensor, stream=None) -> torch.Tensor:
         """The layer forward: one moe_layer_forward call where it serves the

@@ -25,7 +25,7 @@ namespace {
 
 using namespace ffn_dev;
 
-constexpr int BM = 64, BN = 64, BK = 64;  // the general kernel (operands past 32-bit byte offsets, ffn_narrow)
+constexpr int BM = 64, BN = 64, BK = 64;  // the general kernel (operands past 32-bit byte offsets; ffn_narrow)
 constexpr int KCH = BK / 8;               // 16-byte chunks per tile row
 
 // A read of metadata that earlier launches wrote and the grouped GEMM only
@@ -1327,7 +1327,7 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
             // flush the operand panels other workgroups on the die are reusing.
             typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
             const __amdgpu_buffer_rsrc_t pr = __builtin_amdgcn_make_buffer_rsrc(
-                partials, (short)0, (int)((int64_t)2 * ws.G * SLOT * 4), 0x00020000);
+                partials, (short)0, (int)((int64_t)2 * ws.Gsk * SLOT * 4), 0x00020000);
             constexpr int SC1 = 0x10;
             // Small-row tiles move only the 8-row groups of a wave that hold
             // rows of the tile (decode tiles are mostly padding); the group
@@ -1371,7 +1371,7 @@ __device__ __forceinline__ void gemm_class(uint4 *ring, const uint16_t *__restri
             // (NB*4 DMA instructions per wave, 1 KB each) per chunk, two
             // chunks in flight.  Each wave reads back only what its own loads
             // wrote, so waiting for its own loads (vmcnt) is enough.
-            const i32x4_t pdesc = buffer_desc(partials, (int64_t)2 * ws.G * SLOT * 4);
+            const i32x4_t pdesc = buffer_desc(partials, (int64_t)2 * ws.Gsk * SLOT * 4);
             auto add_partial = [&](int c, bool assign) {
                 constexpr int CH = NB * 4;
                 const uint32_t base_c = (uint32_t)(slot_of(c) * SLOT * 4);
@@ -1892,28 +1892,40 @@ SchedShape sched_shape(int H, int Is, int grid)
     return sh;
 }
 
+// Widths the large-tile kernels serve (multiples of 8, which every entry
+// point checks): small enough that a row's offsets and the tile numbers fit.
+bool ffn_widths(int H, int Is) { return H <= (1 << 26) && Is <= (1 << 26); }
+
+// Experts with a few hundred KB of weights, in widths that are not whole
+// slices: most of a 256-wide tile would be padding, and what the streaming
+// kernels do not serve (ffn_kernels) goes to the general kernel's 64x64 tiles
+// (us, tiled / general, evenly loaded and under a Zipf(1.2) load: 2 experts of
+// H 208, I 32, 4096 rows 30 / 17 and 33 / 17, top-8 over 16 of them, 6000 tokens
+// 63 / 51 and 62 / 51; 8 of H 72, I 40, 9000 rows 32 / 15 and 32 / 15; 64 of H 520,
+// I 72, 9000 rows 41 / 47 and 52 / 45; but 12 of H 1000, I 200, 1.2 MB, 53 / 75).
+bool ffn_narrow(int H, int Is) { return !ffn_whole_slices(H, Is) && (int64_t)6 * H * Is <= (int64_t)256 << 10; }
+
 // Workspace layout of the grouped FFN (every part 256-byte aligned):
 //   prefix large, gate-up and down [El+1] each | prefix small, gate-up and
 //   down [El+1] + small tile height each | class cut, gate-up and down [El] each |
 //   small m-tiles (expert, first row, end row), gate-up and down [mts] each |
 //   tile counters: large gate-up, large down, small gate-up, small down |
-//   split-K partial slots: small [2*G][SLOT_SMALL], large [2*G][SLOT_BIG] fp32 |
+//   split-K partial slots: small [..][SLOT_SMALL], large [..][SLOT_BIG] fp32 |
 //   h [cap, I_s] bf16
 // The two GEMMs run one after the other on the stream and share the partial
-// slots; each keeps its own tile counters.
-// Widths the large-tile kernels serve (multiples of 8, which every entry
-// point checks): small enough that a row's offsets and the tile numbers fit.
-bool ffn_widths(int H, int Is) { return H <= (1 << 26) && Is <= (1 << 26); }
-
+// slots; each keeps its own tile counters.  A workgroup has two slots, and
+// there are slots for as many workgroups as pieces can be: of the small class
+// as many as the rows' tiles have K-slices (none where a tile has one), of the
+// large class none unless K is long enough to be split.
 struct FfnLayout {
-    bool big;
+    bool big;  // the tiled kernels serve these widths
     int64_t t_gu, t_dn, ts_gu, ts_dn;  // tile-count bounds per class and GEMM
     int grid;                          // persistent workgroups of a large-tile launch
     size_t off_pre_ld, off_pre_s, off_pre_sd, off_split, off_split_d, off_mt, off_mt_d, off_cnt, off_part_s, off_part,
         off_h, total;
     FfnLayout(int64_t cap, int El, int H, int Is)
     {
-        big = ffn_widths(H, Is);
+        big = ffn_widths(H, Is) && !ffn_narrow(H, Is);
         const int bm = big ? BIGM : BM;
         const int64_t mt = ceil_div(cap, bm) + El;
         t_gu = mt * ceil_div(Is, big ? BIGN / 2 : BN);
@@ -1926,7 +1938,14 @@ struct FfnLayout {
         ts_gu = mts * ceil_div(Is, BIGN / 2);
         ts_dn = mts * ceil_div(H, BIGN);
         grid = device_cus();
-        const size_t slots = big ? 2 * (size_t)grid : 0;
+        const int64_t nk_gu = k_slices(H), nk_dn = k_slices(Is);
+        // (a small m-tile is 64 rows or more, or the last of its expert)
+        const int64_t live = cap / SMALL64.rows + (El < cap ? El : cap), mtl = mts < live ? mts : live;
+        const int64_t pieces_gu = nk_gu > 1 ? mtl * ceil_div(Is, BIGN / 2) * nk_gu : 0;
+        const int64_t pieces_dn = nk_dn > 1 ? mtl * ceil_div(H, BIGN) * nk_dn : 0;
+        const int64_t pieces = pieces_gu > pieces_dn ? pieces_gu : pieces_dn;
+        const size_t slots_s = big ? 2 * (size_t)(pieces < grid ? pieces : grid) : 0;
+        const size_t slots_l = big && (nk_gu >= SPLIT_MIN_NK || nk_dn >= SPLIT_MIN_NK) ? 2 * (size_t)grid : 0;
         off_pre_ld = align256((size_t)(El + 1) * sizeof(int32_t));
         off_pre_s = off_pre_ld + align256((size_t)(El + 1) * sizeof(int32_t));
         off_pre_sd = off_pre_s + align256((size_t)(El + 2) * sizeof(int32_t));
@@ -1936,8 +1955,8 @@ struct FfnLayout {
         off_mt_d = off_mt + align256((size_t)mts * sizeof(int4));
         off_cnt = off_mt_d + align256((size_t)mts * sizeof(int4));
         off_part_s = off_cnt + align256((size_t)(t_gu + t_dn + ts_gu + ts_dn) * sizeof(int32_t));
-        off_part = off_part_s + align256(slots * SLOT_SMALL * sizeof(float));
-        off_h = off_part + align256(slots * SLOT_BIG * sizeof(float));
+        off_part = off_part_s + align256(slots_s * SLOT_SMALL * sizeof(float));
+        off_h = off_part + align256(slots_l * SLOT_BIG * sizeof(float));
         total = off_h + align256((size_t)cap * Is * 2);
     }
 };
@@ -1961,21 +1980,6 @@ bool ffn_large_tiles(int64_t x_rows, int64_t rows, int H, int Is)
 
 namespace {
 
-// Many rows of experts with a few hundred KB of weights, in widths that are
-// not whole slices: most of a 256-wide tile would be padding, and the general
-// kernel's 64x64 tiles take less (us, tiled / general, evenly loaded and under a
-// Zipf(1.2) load: 2 experts of H 208, I 32, 4096 rows 30 / 17 and 33 / 17, top-8 over
-// 16 of them, 6000 tokens 63 / 51 and 62 / 51; 8 of H 72, I 40, 9000 rows 32 / 15 and
-// 32 / 15; 64 of H 520, I 72, 9000 rows 41 / 47 and 52 / 45; but 12 of H 1000, I 200,
-// 1.2 MB, 53 / 75).  Up to 4096 rows with a mean of at most 256, and up to 3072
-// with any, ffn_kernels takes the streaming ones.
-constexpr int64_t NARROW_BYTES = (int64_t)256 << 10;
-bool ffn_narrow(int64_t rows, int64_t R, int H, int Is)
-{
-    return !ffn_whole_slices(H, Is) && (int64_t)6 * H * Is <= NARROW_BYTES &&
-           (rows > 4096 || (rows > 3072 && R > 256));
-}
-
 // One grouped-FFN call: its row space (the routed rows [0, cap), then the
 // shared expert's rows), the workspace parts and the schedule's arguments.
 struct FfnCall {
@@ -1983,7 +1987,8 @@ struct FfnCall {
     int El, ne, H, Is;
     int64_t cap, sc, rows, n_cnt;
     int64_t pairs;  // most routed rows, by which the kernels and their shapes are chosen
-    bool big;
+    bool fits;   // operands within 32-bit byte offsets: the tiled and the streaming kernels can run
+    bool big;    // the tiled kernels run what the streaming ones do not (else the general kernel)
     int32_t *pre, *pre_ld, *pre_s, *pre_sd, *split, *split_d, *cnt;
     int4 *mt_g, *mt_d;
     float *part_s, *part;
@@ -2008,8 +2013,8 @@ struct FfnCall {
         part = reinterpret_cast<float *>(base + L.off_part);
         h = reinterpret_cast<uint16_t *>(base + L.off_h);
         h_sh = h + cap * Is;  // the shared expert's h rows
-        big = ffn_large_tiles(gather ? x_rows : rows, rows, H, Is) &&
-              !ffn_narrow(gather ? x_rows : rows, ceil_div(pairs, El), H, Is);
+        fits = ffn_large_tiles(gather ? x_rows : rows, rows, H, Is);
+        big = fits && L.big;
         n_cnt = big ? L.t_gu + L.t_dn + L.ts_gu + L.ts_dn : 0;
         sh = sched_shape(H, Is, L.grid);
         so = SchedOut{{pre, pre_ld}, {pre_s, pre_sd}, {split, split_d}, {mt_g, mt_d}};
@@ -2072,18 +2077,19 @@ struct FfnCall {
 constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20, SMALL_EXPERT_BYTES = (int64_t)10 << 20,
                   MID_EXPERT_BYTES = (int64_t)48 << 20, RAGGED_SMALL_BYTES = (int64_t)8 << 20,
                   RAGGED_MID_BYTES = (int64_t)2 << 20, RAGGED_MID_PAIRS = 20000;
-enum FfnKernels { FFN_TILED, FFN_STREAM, FFN_MID };
+enum FfnKernels { FFN_TILED /* or general: FfnCall::big */, FFN_STREAM, FFN_MID };
 FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
 {
-    if (!c.big || c.H > (1 << 20) || c.Is > (1 << 20)) return FFN_TILED;
+    if (!c.fits || c.H > (1 << 20) || c.Is > (1 << 20)) return FFN_TILED;
     const int64_t rows = gather ? x_rows : c.rows, R = ceil_div(c.pairs, c.El);
     const int64_t bytes = (int64_t)6 * c.H * c.Is;  // an expert's weights
     if (rows <= 64) return FFN_STREAM;
     if (c.El * bytes <= STREAM_CACHED_BYTES && rows <= 512) return FFN_STREAM;
     if (!ffn_whole_slices(c.H, c.Is)) {
         if (rows > 4096) return FFN_TILED;
-        if (bytes > NARROW_BYTES && (bytes <= RAGGED_MID_BYTES ? c.pairs > RAGGED_MID_PAIRS
-                                                               : R > (bytes <= RAGGED_SMALL_BYTES ? 256 : 96)))
+        if (ffn_narrow(c.H, c.Is) ? rows > 3072 && R > 256
+                                  : bytes <= RAGGED_MID_BYTES ? c.pairs > RAGGED_MID_PAIRS
+                                                              : R > (bytes <= RAGGED_SMALL_BYTES ? 256 : 96))
             return FFN_TILED;
         return R <= 48 && rows <= 3072 ? FFN_STREAM : FFN_MID;
     }

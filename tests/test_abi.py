@@ -45,6 +45,20 @@ def test_workspace_sizes():
     assert moe.ffn_workspace_size(8192, 0, 4096, 1792) == 0
 
 
+def test_ffn_workspace_parts():
+    """The partial sums' slots: none for narrow experts, few for few rows, at most two per compute unit."""
+    MB = 1 << 20
+    size = moe.ffn_workspace_size
+    assert size(64, 8, 208, 32) <= 5888 and size(64, 8, 72, 40) <= 64 * 40 * 2 + 2048
+    assert size(2, 8, 1000, 200) <= 20 * MB
+    for cap, El, H, Is in ((16408, 128, 2048, 96), (8192, 8, 4096, 1792), (2400, 12, 1000, 1208), (64, 8, 4096, 1536)):
+        assert size(cap, El, H, Is) <= 64 * MB + cap * Is * 2 + MB
+    for H, Is in ((264, 8248), (8192, 256)):
+        assert size(64, 8, H, Is) >= 128 * MB
+    # the layer's workspace is the permutation's and the grouped FFN's
+    assert moe.layer_workspace_size(100, 2, 8, 1000, 200) == moe.permute_workspace_size(100, 2, 8) + size(200, 8, 1000, 200)
+
+
 @pytest.mark.parametrize("T,E,k,st", [(4, 8, 0, INVALID), (4, 8, 9, INVALID), (4, 0, 1, INVALID),
                                       (-1, 8, 2, INVALID), (4, 2048, 2, UNSUPPORTED),
                                       (4, 64, 17, UNSUPPORTED), (1 << 29, 64, 8, UNSUPPORTED)])

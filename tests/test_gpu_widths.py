@@ -7,7 +7,7 @@ import torch
 
 import moe_inputs as mi
 import paper_2606_26607_amd as moe
-from tests.util import assert_close_rel, bf16_f64, dev_bf16, host_bf16
+from tests.util import assert_close_rel, bf16_f64, dev_bf16, ffn_route, host_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -112,3 +112,28 @@ def test_operand_beyond_4gib(oracle):
     rows = host_bf16(x[-500:].contiguous())[r2p - (T - 500)]
     ref = oracle.grouped_ffn(rows, offs, w13, w2)
     assert_close_rel(bf16_f64(host_bf16(y)), ref, what="x above 4 GiB")
+
+
+@pytest.mark.parametrize("El,H,Is,rows,T,route", [
+    (8, 1000, 200, [9, 0, 20, 1, 30, 0, 3, 1], 5000, "tiled"),        # few rows gathered from many tokens
+    (4, 264, 8248, [300, 64, 0, 57], 0, "tiled"),                     # split over K in both classes
+    (2, 8200, 136, [70, 40], 4200, "tiled"),
+    (3, 4096, 1600, [90, 300, 33], 0, "tiled"), (3, 512, 640, [600, 64, 257], 0, "tiled"),   # whole slices
+    (8, 72, 40, [1, 0, 700, 3, 2500, 9, 0, 1], 0, "general"), (8, 72, 40, [1, 0, 70, 3, 25, 9, 0, 1], 0, "streaming")])
+def test_workspace_is_enough(oracle, El, H, Is, rows, T, route):
+    """A call writes inside the workspace it asks for, and its parts do not overlap."""
+    n, k = sum(rows), 2
+    offs = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    x = mi.random_bf16((T or n, H), seed=H, tag=100)
+    w13 = mi.random_bf16((El, 2 * Is, H), seed=H, tag=101, std=0.05)
+    w2 = mi.random_bf16((El, H, Is), seed=H, tag=102, std=0.05)
+    r2p = np.random.default_rng(H).integers(0, T * k, n).astype(np.int32) if T else None
+    need = moe.ffn_workspace_size(n, El, H, Is)
+    ws = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+    y = torch.empty((n, H), dtype=torch.bfloat16, device="cuda")
+    args = (dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2),
+            None if r2p is None else torch.from_numpy(r2p).cuda(), k)
+    assert ffn_route(lambda: moe.grouped_ffn(*args, cap_rows=n, y=y, workspace=ws[:need])) == route
+    assert bool((ws[need:] == 0x5A).all())
+    assert_close_rel(bf16_f64(host_bf16(y)), oracle.grouped_ffn(x if r2p is None else x[r2p // k], offs, w13, w2),
+                     what=f"H={H} Is={Is} {rows}")
