@@ -408,9 +408,9 @@ typedef enum moe_kernel_kind {
     MOE_K_SPLITK_REDUCE = 7, /* combination of split-K partials of the large tiles (long K only) */
     MOE_K_RESHARD = 8,       /* expert-weight resharding */
     MOE_K_KV_MOVE = 9,       /* paged KV head moves (and their slot expansion) */
-    MOE_K_LAYER_PREP = 10,   /* moe_layer_forward: the launches that prepare the FFN: the permutation (decode), or
-                                the fused permutation and tile schedule (with routing on larger inputs; on smaller
-                                ones routing is timed as MOE_K_ROUTE) */
+    MOE_K_LAYER_PREP = 10,   /* moe_layer_forward: launches that do more than one call's step: the permutation with
+                                the tile schedule (with routing and the permutation's histogram on larger inputs),
+                                or, for few tokens and experts without a schedule, routing with the permutation */
     MOE_K_COUNT = 11
 } moe_kernel_kind;
 

@@ -2392,11 +2392,11 @@ hipError_t launch_route_perm(const float *logits, int64_t T, int E, int k, int e
 // the separate calls.
 hipError_t launch_route_permute(const float *logits, int64_t T, int E, int k, int e0, int El, int32_t *ids, float *w,
                                 int32_t *counts, int32_t *offsets, int32_t *r2p, int32_t *p2r, int64_t cap,
-                                int32_t *ws_perm, int kind, hipStream_t s)
+                                int32_t *ws_perm, hipStream_t s)
 {
     hipError_t err;
     if (route_in_one_workgroup(T, E, k, El)) {
-        KernelTimer timer(kind, s);
+        KernelTimer timer(MOE_K_LAYER_PREP, s);
         return launch_route_perm(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, s);
     }
     const int64_t nchunks = permute_chunks(T, k, El);
@@ -2407,11 +2407,11 @@ hipError_t launch_route_permute(const float *logits, int64_t T, int E, int k, in
                                                permute_dev::chunk_pairs(T * k, El) == 256, s);
             if (err != hipSuccess) return err;
         }
-        KernelTimer timer(kind, s);
+        KernelTimer timer(MOE_K_PERMUTE, s);
         return launch_scan_scatter(ids, T, k, e0, El, counts, offsets, r2p, p2r, ws_perm, s);
     }
     if ((err = launch_route(logits, T, E, k, ids, w, s)) != hipSuccess) return err;
-    return launch_permute(ids, T, k, e0, El, counts, offsets, r2p, p2r, nullptr, 0, nullptr, cap, ws_perm, s, kind);
+    return launch_permute(ids, T, k, e0, El, counts, offsets, r2p, p2r, nullptr, 0, nullptr, cap, ws_perm, s);
 }
 
 }  // namespace
@@ -2437,7 +2437,7 @@ hipError_t launch_layer(const uint16_t *x, const float *logits, int64_t T, int E
     if (!layer_fused_prep(T, k, El, H, Is, sc)) {
         // (the streaming GEMMs take no schedule, so this serves them too)
         if ((err = launch_route_permute(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, cap, ws_perm,
-                                        MOE_K_PERMUTE, s)) != hipSuccess)
+                                        s)) != hipSuccess)
             return err;
         if ((err = launch_grouped_ffn(x, T, r2p, k, offsets, El, cap, H, Is, w13, w2, y, sb, sc, sw13, sw2,
                                       shared_y, ws_ffn, s)) != hipSuccess)
@@ -2449,8 +2449,7 @@ hipError_t launch_layer(const uint16_t *x, const float *logits, int64_t T, int E
     if (which != FFN_TILED) {
         // these GEMMs take no tile schedule: the permutation is all the
         // preparation
-        const int kind = layer_fused_prep(T, k, El, H, Is, sc) ? MOE_K_LAYER_PREP : MOE_K_PERMUTE;
-        if ((err = launch_route_permute(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, cap, ws_perm, kind,
+        if ((err = launch_route_permute(logits, T, E, k, e0, El, ids, w, counts, offsets, r2p, p2r, cap, ws_perm,
                                         s)) != hipSuccess)
             return err;
         if ((err = launch_stream_gemms(c, which, x, T, r2p, k, offsets, w13, w2, y, sb, sw13, sw2, shared_y, s)) != hipSuccess)

@@ -74,7 +74,7 @@ hipError_t permute_scratch(int32_t **ptr);
 hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, int32_t *counts,
                           int32_t *offsets, int32_t *row_to_pair, int32_t *pair_to_row,
                           const uint16_t *x, int H, uint16_t *x_perm, int64_t cap, int32_t *ws,
-                          hipStream_t s, int kind = MOE_K_PERMUTE);
+                          hipStream_t s);
 
 size_t ffn_workspace_bytes(int64_t cap, int El, int H, int Is);
 // Widths made of whole 64-wide K-slices, two at least: what a shared expert's

@@ -366,7 +366,7 @@ hipError_t launch_scan_scatter(const int32_t *ids, int64_t T, int k, int e0, int
 hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, int32_t *counts,
                           int32_t *offsets, int32_t *row_to_pair, int32_t *pair_to_row,
                           const uint16_t *x, int H, uint16_t *x_perm, int64_t cap, int32_t *ws,
-                          hipStream_t s, int kind)
+                          hipStream_t s)
 {
     const int64_t npairs = T * k;
     const int64_t nchunks = permute_chunks(T, k, El);
@@ -374,7 +374,7 @@ hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, 
     const int nbits = permute_bits(El);
     hipError_t err;
     if (permute_one_workgroup(npairs, El)) {
-        KernelTimer timer(kind, s);
+        KernelTimer timer(MOE_K_PERMUTE, s);
         if (El <= 64)
             permute_small_kernel<64><<<dim3(1), dim3(1024), 0, s>>>(ids, npairs, e0, El, nbits, counts, offsets,
                                                                      row_to_pair, pair_to_row);
@@ -383,7 +383,7 @@ hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, 
                                                                               offsets, row_to_pair, pair_to_row);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     } else {
-        KernelTimer timer(kind, s);
+        KernelTimer timer(MOE_K_PERMUTE, s);
         if (nchunks > 0) {
             if (short_chunks)
                 count_kernel<4><<<dim3((unsigned)nchunks), dim3(64), El * sizeof(int32_t), s>>>(

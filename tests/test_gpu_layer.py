@@ -13,7 +13,7 @@ import torch
 
 import moe_inputs as mi
 import paper_2606_26607_amd as moe
-from tests.util import dev_bf16, host_bf16
+from tests.util import dev_bf16, host_bf16, launched
 
 pytestmark = pytest.mark.gpu
 
@@ -52,14 +52,9 @@ def both_paths(cfg, x=None, lg=None):
     ref = snapshot(layer)
     for t in (layer.topk_ids, layer.topk_w, layer.y, layer.out, *layer.bufs.values()):
         t.view(torch.uint8).fill_(0xA5)  # the one call must write everything again
-    moe.timing_reset()
-    moe.timing_enable(True)
-    layer.forward(x, lg)
-    torch.cuda.synchronize()
-    moe.timing_enable(False)
+    kinds = launched(lambda: layer.forward(x, lg))
     got = snapshot(layer)
-    _, fused = moe.timing_read("layer_prep")
-    return ref, got, fused
+    return ref, got, kinds
 
 
 def assert_same(ref, got, what):
@@ -71,12 +66,14 @@ def assert_same(ref, got, what):
 @pytest.mark.parametrize("name", list(mi.CONFIGS))
 def test_one_call_equals_four_calls(name):
     cfg = mi.CONFIGS[name]
-    ref, got, fused = both_paths(cfg)
+    ref, got, kinds = both_paths(cfg)
     assert_same(ref, got, cfg.name)
-    # every workload has at most 64 local experts and large-tile shapes except
-    # the tiny one (H = 256, I = 512: large-tile shapes too): all take the
-    # fused launches
-    assert fused >= 1
+    # the tiled workloads schedule in the permutation's launch; the two whose
+    # GEMMs stream take no schedule: the tiny one routes and permutes in one
+    # launch, the 64-token one (256 experts) in two
+    assert "schedule" not in kinds
+    assert kinds.get("layer_prep", 0) == (0 if name == "c5a" else 1)
+    assert ("permute" in kinds) == (name == "c5a")
 
 
 @pytest.mark.parametrize("T,H,E,k,I,P,layout,shared,fused", [
@@ -86,12 +83,13 @@ def test_one_call_equals_four_calls(name):
     (7000, 128, 64, 6, 128, 1, "replicated", False, True),    # 64 local experts, 6 pairs per token
     (300000, 128, 64, 8, 128, 8, "ep", False, True),          # pairs x experts above 2^24: 1024-pair chunks
     (4096, 1024, 256, 8, 512, 8, "ep", True, True),           # shared expert, two fused launches
-    (700, 256, 128, 4, 256, 1, "replicated", False, False),   # 128 local experts: the four calls' launches
-    (700, 136, 8, 2, 256, 1, "replicated", False, False),     # H not a multiple of 64: the general GEMM path
+    (700, 256, 128, 4, 256, 1, "replicated", False, False),   # 128 local experts: a schedule of its own
+    (700, 136, 8, 2, 256, 1, "replicated", False, False),     # H not a multiple of 64: the streaming GEMMs
     (0, 256, 8, 2, 256, 1, "replicated", False, False),       # no tokens
 ])
 def test_one_call_edges(T, H, E, k, I, P, layout, shared, fused):
     cfg = mi.MoeConfig("edge", T=T, H=H, E=E, k=k, I=I, P=P, layout=layout, shared=shared, seed=T + E + k)
-    ref, got, nfused = both_paths(cfg)
+    ref, got, kinds = both_paths(cfg)
     assert_same(ref, got, f"T={T} H={H} E={E} k={k} {layout}{P}")
-    assert (nfused > 0) == fused
+    assert ("layer_prep" in kinds) == fused
+    assert ("schedule" in kinds) == (E == 128)
