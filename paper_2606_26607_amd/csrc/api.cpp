@@ -125,7 +125,7 @@ extern "C" moe_status moe_permute(const int32_t *topk_ids, int64_t T, int k, int
     if (!workspace || workspace_bytes < need)
         return fail(MOE_ERR_WORKSPACE, "moe_permute: workspace %zu < %zu bytes", workspace_bytes, need);
     const int64_t cap = T * (k < El ? k : El);
-    return hip_status(launch_permute(topk_ids, T, k, expert_begin, El, counts, offsets, row_to_pair,
+    return hip_status(launch_permute(topk_ids, T, k, E, expert_begin, El, counts, offsets, row_to_pair,
                                      pair_to_row, x, H, x_perm, cap, static_cast<int32_t *>(workspace),
                                      (hipStream_t)stream),
                       "moe_permute launch");
@@ -161,7 +161,7 @@ extern "C" moe_status moe_permute_noalloc(const int32_t *topk_ids, int64_t T, in
     int32_t *scratch = nullptr;
     if ((st = hip_status(permute_scratch(&scratch), "moe_permute_noalloc scratch")) != MOE_OK) return st;
     const int64_t cap = T * (k < El ? k : El);
-    return hip_status(launch_permute(topk_ids, T, k, expert_begin, El, counts, offsets, row_to_pair, pair_to_row,
+    return hip_status(launch_permute(topk_ids, T, k, E, expert_begin, El, counts, offsets, row_to_pair, pair_to_row,
                                      x, H, x_perm, cap, scratch, (hipStream_t)stream),
                       "moe_permute_noalloc launch");
 }

@@ -2411,7 +2411,7 @@ hipError_t launch_route_permute(const float *logits, int64_t T, int E, int k, in
         return launch_scan_scatter(ids, T, k, e0, El, counts, offsets, r2p, p2r, ws_perm, s);
     }
     if ((err = launch_route(logits, T, E, k, ids, w, s)) != hipSuccess) return err;
-    return launch_permute(ids, T, k, e0, El, counts, offsets, r2p, p2r, nullptr, 0, nullptr, cap, ws_perm, s);
+    return launch_permute(ids, T, k, E, e0, El, counts, offsets, r2p, p2r, nullptr, 0, nullptr, cap, ws_perm, s);
 }
 
 }  // namespace

@@ -13,8 +13,8 @@
 //               base + earlier pairs of that expert in the chunk + its rank
 //               among equal lanes.  No global atomics: the result is the
 //               unique stable order, identical on every run.
-//   4. gather:  optional copy of x rows into permuted order (each token read
-//               once, 16-byte moves).
+//   4. gather:  optional copy of x rows into permuted order (16-byte moves;
+//               each token read once where most have rows here).
 // Small inputs (decode: at most 16384 pairs over at most 256 local experts,
 // and a bounded amount of ballot work, see SMALL_WORK) run steps 1-3 in one
 // workgroup instead, saving launches; larger ones with at most 256 local
@@ -292,6 +292,28 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint16_t *__restrict_
     }
 }
 
+// The gather by output row, where few tokens have one here (an EP rank's own
+// experts): by token, every token's slots are looked at, wanted or not.  us,
+// permutation and gather, by token / by row: 8192 tokens of H 4096, one of 8
+// experts, top-2, 23.8 / 16.7; 65536 of them 62.1 / 54.6; 12 of 96, top-5, H 1000
+// 13.8 / 13.3; but with a row a token on average (65536 tokens of H 7168, 32 of 256
+// experts, top-8) 338 / 379.
+__global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t *__restrict__ x, int H, int k,
+                                                          const int32_t *__restrict__ row_to_pair,
+                                                          const int32_t *__restrict__ offsets, int El, int64_t cap,
+                                                          uint16_t *__restrict__ x_perm)
+{
+    int64_t n = offsets[El];
+    if (n > cap) n = cap;
+    const int vecs = H / 8;
+    for (int64_t r = blockIdx.x; r < n; r += gridDim.x) {
+        const int64_t t = row_to_pair[r] / k;
+        const uint4 *src = reinterpret_cast<const uint4 *>(x + t * H);
+        uint4 *dst = reinterpret_cast<uint4 *>(x_perm + r * H);
+        for (int i = threadIdx.x; i < vecs; i += 256) dst[i] = src[i];
+    }
+}
+
 // Outputs above this are stored past the caches.  Routing, permutation and
 // gather, us with cached / non-temporal stores: 2048 tokens of H 7168 to 8 rows
 // each (235 MB) 74.6 / 66.1, 1000 tokens (115 MB) 43.1 / 38.7, 8192 tokens of H 4096
@@ -363,7 +385,7 @@ hipError_t launch_scan_scatter(const int32_t *ids, int64_t T, int k, int e0, int
     return hipGetLastError();
 }
 
-hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, int32_t *counts,
+hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int E, int e0, int El, int32_t *counts,
                           int32_t *offsets, int32_t *row_to_pair, int32_t *pair_to_row,
                           const uint16_t *x, int H, uint16_t *x_perm, int64_t cap, int32_t *ws,
                           hipStream_t s)
@@ -419,6 +441,11 @@ hipError_t launch_permute(const int32_t *ids, int64_t T, int k, int e0, int El, 
     }
     if (x_perm != nullptr && cap > 0) {
         KernelTimer timer(MOE_K_GATHER, s);
+        if ((int64_t)k * El < E) {  // less than a row a token under an even load
+            gather_rows_kernel<<<dim3((unsigned)(cap < 4096 ? cap : 4096)), dim3(256), 0, s>>>(
+                x, H, k, row_to_pair, offsets, El, cap, x_perm);
+            return hipGetLastError();
+        }
         const int threads = H / 8 >= 256 ? 256 : (int)ceil_div(H / 8, 64) * 64;
         const int64_t items = T * ceil_div(H / 8, threads);
         const dim3 grid((unsigned)(items < 16384 ? items : 16384));

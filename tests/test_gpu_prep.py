@@ -41,6 +41,8 @@ def test_permute_wide(oracle, T, E, k, e0, El):
     (1, 8, 16, 16, 0, 16), (300, 8, 8, 2, 2, 2),        # one vector a row; tokens with no row here
     (77, 520, 32, 16, 5, 9), (50, 2040, 8, 3, 0, 8),    # last chunk partly filled; one vector below a whole one
     (33, 2056, 8, 2, 4, 4), (20000, 64, 8, 4, 0, 8),    # second chunk of one vector; several tokens a workgroup
+    (1000, 4096, 8, 2, 7, 1), (5000, 264, 96, 5, 12, 12),  # by row: less than a row a token
+    (70000, 8, 256, 8, 8, 31), (70000, 8, 256, 8, 8, 32),  # ... several rows a workgroup; one row a token
     (1281, 4096, 16, 8, 0, 16), (1280, 4096, 16, 8, 0, 16)])  # either side of the 80 MiB of cached stores
 def test_gather(T, H, E, k, e0, El):
     """The gathered rows are the tokens' own, bit for bit; rows past the last one stay as they were."""
