@@ -12,7 +12,7 @@ import torch
 
 import moe_inputs as mi
 import paper_2606_26607_amd as moe
-from tests.util import W_ATOL, assert_close_rel, bf16_f64, dev_bf16, host_bf16
+from tests.util import W_ATOL, assert_close_rel, bf16_f64, dev_bf16, ffn_route, host_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -114,13 +114,13 @@ def test_permute_configs(oracle, name):
                                      (40000, 512, 8, 8), (448, 64, 8, 1), (456, 64, 8, 1)])
 def test_permute_every_rank(oracle, T, E, k, P):
     """Every rank's slice of the same routing, against the oracle.  Small
-    inputs run in one workgroup: at most 16384 pairs, 64 local experts and
+    inputs run in one workgroup: at most 16384 pairs, 256 local experts and
     32768 pair-steps of ballot work (pairs x (index bits + 2)), so 3584 pairs
     over 64 experts do and 3648 do not; above that pairs x local experts up
     to 2^24 take 256-pair chunks, larger ones 1024-pair chunks (20000 x 8
     pairs over 256 experts and 8192 x 8 over 256 sit on either side of that
     line, and 40000 x 8 pairs over 64 local experts is past it), with the
-    scan and the scatter in one launch for up to 64 local experts."""
+    scan and the scatter in one launch for up to 256 local experts."""
     ids = mi.random_topk_ids(T, E, k, seed=T + E + k)
     total = 0
     for r in range(P):
@@ -236,17 +236,18 @@ def test_grouped_ffn_fused_gather(oracle, El, E, H, Is, T, k, e0):
     assert_close_rel(got, ref, what=f"fused El={El} H={H} Is={Is}")
 
 
-@pytest.mark.parametrize("El,E,H,Is,T,k,e0,sb,sc", [(4, 8, 256, 192, 150, 2, 2, 10, 40),
-                                                    (3, 3, 512, 256, 300, 1, 0, 0, 300),
-                                                    (1, 2, 512, 8192, 300, 1, 0, 50, 250),
-                                                    (8, 8, 256, 128, 200, 2, 0, 0, 0),
-                                                    (2, 16, 7168 // 4, 512, 64, 8, 6, 56, 8)])
-def test_grouped_ffn_shared(oracle, El, E, H, Is, T, k, e0, sb, sc):
+@pytest.mark.parametrize("El,E,H,Is,T,k,e0,sb,sc,route", [
+    (4, 8, 256, 192, 150, 2, 2, 10, 40, "streaming"), (3, 3, 512, 256, 300, 1, 0, 0, 300, "streaming"),
+    (1, 2, 512, 8192, 300, 1, 0, 50, 250, "tiled"), (8, 8, 256, 128, 200, 2, 0, 0, 0, "streaming"),
+    (2, 16, 7168 // 4, 512, 64, 8, 6, 56, 8, "streaming"),
+    (8, 8, 256, 192, 700, 2, 0, 10, 40, "tiled"), (3, 8, 512, 256, 700, 2, 2, 50, 600, "tiled")])
+def test_grouped_ffn_shared(oracle, El, E, H, Is, T, k, e0, sb, sc, route):
     """Routed experts and a shared expert in the same launches: the routed
     rows equal moe_grouped_ffn's result (oracle on the gathered rows), the
     shared rows the shared expert's FFN on x[sb:sb+sc].  Covers a shared
-    expert in the small-row class, in the large class, in a long-K split
-    (the separate reduction writes its rows) and none at all."""
+    expert in the streaming kernels and, tiled, in the small-row class, in the
+    large class, in a long-K split (the separate reduction writes its rows),
+    and none at all."""
     ids = mi.random_topk_ids(T, E, k, seed=T + H + sc)
     _, offs, r2p, _ = oracle.permute(ids, e0, El)
     n = int(offs[-1])
@@ -258,8 +259,10 @@ def test_grouped_ffn_shared(oracle, El, E, H, Is, T, k, e0, sb, sc):
     cap = T * min(k, El)
     r2p_dev = torch.full((cap,), -1, dtype=torch.int32)
     r2p_dev[:n] = torch.from_numpy(r2p)
-    y, sy = moe.grouped_ffn_shared(dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2),
-                                   r2p_dev.cuda(), k, cap, sb, sc, dev_bf16(sw13), dev_bf16(sw2))
+    args = (dev_bf16(x), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2), r2p_dev.cuda(), k, cap, sb, sc,
+            dev_bf16(sw13), dev_bf16(sw2))
+    assert ffn_route(lambda: moe.grouped_ffn_shared(*args)) == route
+    y, sy = moe.grouped_ffn_shared(*args)
     torch.cuda.synchronize()
     got = bf16_f64(host_bf16(y)[:n])
     ref = oracle.grouped_ffn(x[r2p // k], offs, w13, w2)

@@ -1,6 +1,7 @@
 """Widths that are not whole 64-wide K-slices (needs an MI355X): the last
-slice of either GEMM is partly past K, and its loads read zeros there.  Every
-case is checked against the CPU oracle."""
+slice of either GEMM is partly past K, and its loads read zeros there, in the
+streaming, mid and tiled kernels.  Every case is checked against the CPU
+oracle."""
 import numpy as np
 import pytest
 import torch
@@ -19,7 +20,7 @@ def _gpu():
     moe.lib()
 
 
-# rows per expert: whole and partial 256-row tiles, 64- and 128-row ones, single rows, none
+# rows per expert: several passes of a streaming kernel, whole and partial ones, single rows, none
 ROWS = [300, 0, 64, 120, 1, 513, 17]
 
 
@@ -44,6 +45,38 @@ def test_partial_last_slice(oracle, H, Is, gather):
     torch.cuda.synchronize()
     ref = oracle.grouped_ffn(x if r2p is None else x[r2p // k], offs, w13, w2)
     assert_close_rel(bf16_f64(host_bf16(y)), ref, what=f"H={H} Is={Is} gather={gather}")
+
+
+# ... and with enough rows for the tiled kernels: whole and partial 256-row tiles, 64- and 128-row ones
+TILED_ROWS = [3000, 0, 64, 120, 1, 900, 17]
+
+
+@pytest.mark.parametrize("rows,T,H,Is", [
+    (TILED_ROWS, 0, 1000, 328), (TILED_ROWS, 4200, 1000, 328),
+    (TILED_ROWS, 0, 136, 352), (TILED_ROWS, 4200, 1032, 72),    # one chunk past a slice, in either GEMM
+    (TILED_ROWS, 0, 56, 1016), (TILED_ROWS, 0, 1016, 56),       # one slice; one short of a chunk
+    ([300, 64, 0, 57], 0, 264, 8248), ([70, 40], 4200, 8200, 136)])  # split over K, the last piece partial
+def test_tiles_mask_the_last_slice(oracle, rows, T, H, Is):
+    """What lies past K is the next row's: with infinities there, in the activations and in the down projection's
+    weights, a load that is not masked, of either operand, shows in the row before."""
+    El, k, n = len(rows), 2, sum(rows)
+    offs = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    x = mi.random_bf16((T or n, H), seed=H, tag=110)
+    w13 = mi.random_bf16((El, 2 * Is, H), seed=H, tag=111, std=0.05)
+    w2 = mi.random_bf16((El, H, Is), seed=H, tag=112, std=0.05)
+    r2p = np.random.default_rng(H).integers(0, T * k, n).astype(np.int32) if T else None
+    tokens = np.arange(n) if r2p is None else r2p // k
+    ref = oracle.grouped_ffn(x[tokens], offs, w13, w2)
+    inf = mi.f32_to_bf16_bits(np.array([np.inf], np.float32))[0]
+    xi, w2i = x.copy(), w2.copy()
+    xi[1::2, :8] = inf
+    w2i[:, 1::2, :8] = inf
+    y = torch.empty((n, H), dtype=torch.bfloat16, device="cuda")
+    args = (dev_bf16(xi), torch.from_numpy(offs).cuda(), dev_bf16(w13), dev_bf16(w2i),
+            None if r2p is None else torch.from_numpy(r2p).cuda(), k)
+    assert ffn_route(lambda: moe.grouped_ffn(*args, cap_rows=n, y=y)) == "tiled"
+    even = tokens % 2 == 0
+    assert_close_rel(bf16_f64(host_bf16(y))[even][:, 0::2], ref[even][:, 0::2], what=f"H={H} Is={Is} T={T}")
 
 
 @pytest.mark.parametrize("H,Is,rows", [
@@ -82,7 +115,7 @@ def test_small_weights_layer(oracle, T, H, I):
 
 
 def test_infinite_neighbour(oracle):
-    """A row's neighbour in memory holds infinities: they stay out of the row's own result."""
+    """A row's neighbour in memory holds infinities: they stay out of the row's own result (streaming kernels)."""
     H, Is, n = 200, 72, 300
     x = mi.random_bf16((n, H), seed=5, tag=73)
     x[1::2, :8] = mi.f32_to_bf16_bits(np.array([np.inf], np.float32))[0]

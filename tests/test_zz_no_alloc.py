@@ -5,7 +5,7 @@ Both are called on the same routing; every output must be identical.  Two
 calls in a row, the second on a smaller input, check that the static
 scratch the first call left behind does not leak into the second; every
 path that uses the scratch is covered (256- and 1024-pair chunks, the
-combined scan-and-scatter launch for at most 64 local experts and the
+combined scan-and-scatter launch for at most 256 local experts and the
 separate scan above that), and the one-workgroup path, which uses none.
 """
 import ctypes
@@ -64,10 +64,11 @@ def run_pair(T, E, k, e0, El, seed, H=64):
 
 
 @pytest.mark.parametrize("big,small", [
-    # 256-pair chunks, scan and scatter in one launch (<= 64 local experts)
+    # 256-pair chunks, scan and scatter in one launch (<= 256 local experts)
     ((8192, 128, 8, 0, 16), (3000, 128, 8, 16, 16)),
-    # separate scan (more than 64 local experts)
     ((4096, 256, 8, 0, 256), (1500, 256, 8, 0, 128)),
+    # separate scan (more than 256 local experts)
+    ((4096, 512, 8, 0, 512), (1500, 512, 8, 0, 300)),
     # 1024-pair chunks (pairs x local experts above 2^24), then 256-pair chunks
     ((65536, 64, 8, 0, 64), (9000, 64, 8, 0, 32)),
     # then the one-workgroup path (no scratch), then the chunked one again
