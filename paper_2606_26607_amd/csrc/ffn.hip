@@ -2050,16 +2050,19 @@ struct FfnCall {
 //     111; at 512 138 / 150 and 124 / 161); else up to 768 rows (24 experts of
 //     H 2048, I 768 63 / 54 and 76 / 69; 64 of them, 1536 rows, half of them one
 //     expert's, 138 / 156);
-//   larger experts: gathered, up to 32 experts, 192 tokens and a mean of 40
-//     (48 for fewer than 8 experts), where H is at most 4.5 I (a hot expert's
-//     passes only spread over its I / 16 strips: 128 slices of H 4096, I 768,
-//     128 tokens 433 / 405, but 230 / 269); 32 experts of H 7168, I 2048, 160 tokens
-//     486 / 467 and 165 / 150; else up to 256 rows with a mean of 28 (16 of H
+//   larger experts: gathered, up to 256 tokens and a mean of 48 for up to 16
+//     experts (8 of H 4096, I 1792, top-2, 192 tokens 92 / 89 and 114 / 113; 16 of H
+//     2048, I 1408, top-2, 256 tokens 87 / 69 and 92 / 81), 192 and 40 for up to 32 (of H
+//     7168, I 2048, 160 tokens 486 / 467 and 165 / 150; of H 3072, I 1024, top-8, mean
+//     48, 138 / 146 and 152 / 184), where H is at most 4.5 I (a hot expert's passes
+//     only spread over its I / 16 strips: 128 slices of H 4096, I 768, 128 tokens
+//     433 / 405, but 230 / 269); else up to 256 rows with a mean of 28 (16 of H
 //     4096, I 1536, 256 rows 117 / 101 and 125 / 124; 320 rows of 40 of H 5120, I
 //     1536 320 / 311, but 314 / 329);
-//   top-1 and top-2 layers, mean 88 to 112, up to 512 tokens, mid (8 slices of H
-//     4096, I 2048, 400 tokens 171 / 109 and 171 / 166; below that mean 8 of H 4096,
-//     I 896, 320 tokens 83 / 76, but 76 / 85 under Zipf(0.7); what it costs: an EP
+//   top-1 and top-2 layers, mean 88 (72 past 28 MB) to 112, up to 512 tokens,
+//     mid (8 slices of H 4096, I 1792, 288 tokens 140 / 94 and 147 / 147, I 2048, 400
+//     tokens 171 / 109 and 171 / 166; below that mean 8 of H 4096, I 896, 320 tokens
+//     83 / 76, but 76 / 85 under Zipf(0.7); what it costs: an EP
 //     slice, 8 of 32 experts of H 5120, I 1536, 94 / 88, but 94 / 105).
 // On many rows not gathered nothing but the tiles is safe: the mid kernel
 // takes 155 instead of 245 us for 128 experts of H 2048, I 384, 66 rows each, but
@@ -2075,7 +2078,8 @@ struct FfnCall {
 // 3072 rows (128 of H 2048, I 96, 2100 rows 58 / 40 / 50 and 97 / 54 / 77; 4096 rows,
 // half of them one expert's, 100 / 125 / 96).
 constexpr int64_t STREAM_CACHED_BYTES = (int64_t)16 << 20, SMALL_EXPERT_BYTES = (int64_t)10 << 20,
-                  MID_EXPERT_BYTES = (int64_t)48 << 20, RAGGED_SMALL_BYTES = (int64_t)8 << 20,
+                  MID_LARGE_BYTES = (int64_t)28 << 20, MID_EXPERT_BYTES = (int64_t)48 << 20,
+                  RAGGED_SMALL_BYTES = (int64_t)8 << 20,
                   RAGGED_MID_BYTES = (int64_t)2 << 20, RAGGED_MID_PAIRS = 20000;
 enum FfnKernels { FFN_TILED /* or general: FfnCall::big */, FFN_STREAM, FFN_MID };
 FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
@@ -2099,9 +2103,12 @@ FfnKernels ffn_kernels(const FfnCall &c, int64_t x_rows, bool gather, int k)
         return rows <= 256 && R <= 28 && c.El <= 64 && wide ? FFN_STREAM : FFN_TILED;
     }
     if (c.El < 8) return R <= 48 ? FFN_STREAM : FFN_TILED;
-    if (small ? (rows <= 448 && R <= 28) || (rows <= 256 && R <= 64) : rows <= 192 && R <= 40 && c.El <= 32 && wide)
+    if (small ? (rows <= 448 && R <= 28) || (rows <= 256 && R <= 64)
+              : wide && (c.El <= 16 ? rows <= 256 && R <= 48 : c.El <= 32 && rows <= 192 && R <= 40))
         return FFN_STREAM;
-    return k <= 2 && bytes <= MID_EXPERT_BYTES && rows <= 512 && R >= 88 && R <= 112 ? FFN_MID : FFN_TILED;
+    if (k <= 2 && bytes <= MID_EXPERT_BYTES && rows <= 512 && R >= (bytes > MID_LARGE_BYTES ? 72 : 88) && R <= 112)
+        return FFN_MID;
+    return FFN_TILED;
 }
 
 template <bool GATED>

@@ -1,4 +1,4 @@
-// Device code shared by the grouped-FFN kernels (ffn.hip, ffn_stream.hip).
+// Device code shared by the grouped-FFN kernels (ffn.hip, ffn_stream.h).
 #pragma once
 #include "moe_internal.h"
 

@@ -188,11 +188,14 @@ def test_capacity_leaves_bits_alone(oracle, T, E, k, e0, El, H, Is):
     (72, 1536, 1280, 100, 0, True),
     # gathered: rows is the tokens
     (32, 7168, 256, 64, 8, False), (32, 7168, 256, 65, 8, True), (33, 2048, 1024, 100, 2, True),
-    (16, 2048, 1024, 160, 4, False), (16, 2048, 1024, 161, 4, True), (4, 2048, 1024, 96, 2, False),
+    (16, 2048, 1024, 192, 4, False), (16, 2048, 1024, 193, 4, True), (16, 2048, 1024, 256, 2, False),
+    (16, 2048, 1024, 257, 2, True), (32, 2048, 1024, 160, 8, False), (32, 2048, 1024, 161, 8, True),
+    (32, 2048, 1024, 192, 2, False), (32, 2048, 1024, 193, 2, True), (4, 2048, 1024, 96, 2, False),
     (4, 2048, 1024, 97, 2, True), (8, 2048, 768, 256, 2, False), (8, 2048, 768, 257, 2, True),
     (16, 2048, 512, 448, 1, False), (16, 2048, 512, 449, 1, True),
     (8, 2048, 1024, 348, 2, True), (8, 2048, 1024, 352, 2, False), (8, 2048, 1024, 448, 2, False),
     (8, 2048, 1024, 449, 2, True), (8, 2048, 1024, 400, 3, True),
+    (8, 4096, 1280, 284, 2, True), (8, 4096, 1280, 285, 2, False), (8, 4096, 2112, 400, 2, True),
     # widths that are not whole slices
     (8, 1000, 1208, 2048, 0, False), (8, 1000, 1208, 2049, 0, True), (4, 4096, 360, 384, 0, False),
     (4, 4096, 360, 385, 0, True), (4, 328, 808, 4096, 0, False), (4, 328, 808, 4097, 0, True),
