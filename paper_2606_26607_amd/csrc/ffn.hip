@@ -2036,8 +2036,9 @@ struct FfnCall {
 // one hot expert are better off in 256-row tiles (1 PF and more; the mid
 // kernel does 0.5, the streaming one re-reads the expert's weights every 64
 // rows).  The lines therefore lie where the kernels win under an even load
-// and lose nothing that shows under Zipf(0.7), Zipf(1.2) and half of all rows
-// on one expert, over some 60 layer and FFN shapes of 1 to 256 experts.
+// and, but for the exceptions given, lose no more than 3% under Zipf(0.7),
+// Zipf(1.2) and half of all rows on one expert, over some 60 layer and FFN
+// shapes of 1 to 256 experts.
 // Measured in us, tiled / chosen, evenly loaded and under Zipf(1.2):
 //   at most 64 rows: one expert of H 4096, I 14336, 48 tokens 101 / 73 and 114 /
 //     74; 256 slices of H 7168, I 512, 16 tokens 393 / 366 and 138 / 122, but 64

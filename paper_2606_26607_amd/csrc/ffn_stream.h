@@ -15,10 +15,12 @@
 // end, so launches need no tile schedule, no partial sums in memory and no
 // even split.  An expert without rows ends its workgroups at once.
 //
-// Measured against the tiled kernels (layer, us): DeepSeek-V3-shaped EP slice,
-// 64 tokens 398 -> 370 (6.7 TB/s); Qwen3-shaped TP slice (128 experts, I_s
-// 192), 64 tokens 160 -> 114; Mixtral-shaped TP slice, 1 token 54 -> 33, 64
-// tokens 99 -> 80; the tiny replicated layer 33 -> 21.
+// Measured against the tiled kernels, in turn on one box (layer, replayed from
+// a graph, us): DeepSeek-V3-shaped EP slice, 64 tokens 394 -> 369 (6.7 TB/s; on
+// another box and in a longer graph 409 -> 404); Qwen3-shaped TP slice (128
+// experts, I_s 192), 64 tokens 163 -> 108; Mixtral-shaped TP slice, 1 token 56 ->
+// 29, 64 tokens 91 -> 72; the tiny replicated layer (which now also routes and
+// permutes in one launch) 33 -> 16.
 #pragma once
 #include <type_traits>
 
@@ -467,10 +469,15 @@ __device__ __forceinline__ void mid_rows(const StreamArgs &g, int e, int r0, int
 // whole shader engines with nothing else (120 -> 200 us and more).  Two
 // workgroups a CU: four weight blocks a wave, three workgroups a CU, a second
 // set of buffers or the next slice staged between the MFMAs spill.
-// Measured, us, tiled kernels before: 128 experts of H 4096, I 192, 100 rows
-// each 314 -> 205; 16 of H 2048, I 768 69 -> 49; 8 slices of H 4096, I 1792, 400
-// tokens of a top-2 layer 150 -> 98.  What bounds it is the chain of a slice
-// (registers to LDS, barrier, fragments, MFMAs) at two waves a SIMD: 0.5 PF.
+// Measured (layer, replayed from a graph, us; the kernels before): 8 slices of
+// H 4096, I 1792, 400 tokens of a top-2 layer 147 -> 101 (tiled), 128 of H 2048, I
+// 96, 2051 tokens top-8 192 -> 123 (general).  In the latter the gate-up (43 us)
+// keeps the LDS busy for 48% of the cycles in which its CUs have work, a third
+// of that conflicts, and the matrix cores for 16% of all; its waves wait 29%,
+// two thirds of it for LDS: the chain of a slice (registers to LDS, barrier,
+// fragments, MFMAs) at two waves a SIMD, and its LDS traffic, more than either
+// rate.  The down projection (52 us) has two slices a tile and moves 2.2 TB/s:
+// prologue, epilogue and stores.
 template <bool GATED, bool NT>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * MID_WAVES, 64 * MID_WAVES), amdgpu_waves_per_eu(2)))
 void mid_kernel(StreamArgs g, LaunchStamps ts)
