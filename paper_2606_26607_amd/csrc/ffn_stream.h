@@ -474,10 +474,11 @@ __device__ __forceinline__ void mid_rows(const StreamArgs &g, int e, int r0, int
 // 96, 2051 tokens top-8 192 -> 123 (general).  In the latter the gate-up (43 us)
 // keeps the LDS busy for 48% of the cycles in which its CUs have work, a third
 // of that conflicts, and the matrix cores for 16% of all; its waves wait 29%,
-// two thirds of it for LDS: the chain of a slice (registers to LDS, barrier,
-// fragments, MFMAs) at two waves a SIMD, and its LDS traffic, more than either
-// rate.  The down projection (52 us) has two slices a tile and moves 2.2 TB/s:
-// prologue, epilogue and stores.
+// two thirds of it for LDS; 191 MB come from memory (4.5 TB/s: the weights
+// once, 100 MB, and the activations into each die's L2).  No one rate is the
+// bound: the chain of a slice (registers to LDS, barrier, fragments, MFMAs) at
+// two waves a SIMD is, with that traffic.  The down projection (52 us) has two
+// slices a tile and moves 3.2 TB/s: prologue, epilogue and stores.
 template <bool GATED, bool NT>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * MID_WAVES, 64 * MID_WAVES), amdgpu_waves_per_eu(2)))
 void mid_kernel(StreamArgs g, LaunchStamps ts)
