@@ -156,8 +156,9 @@ moe_status moe_permute_noalloc(const int32_t *topk_ids, int64_t T, int k, int E,
  * Experts with no rows read none of their weights.
  * The order of the fp32 sums, hence the last bit of a result, depends on the
  * sizes that choose the kernels: x_rows, k, El, H, I_s (and a shared expert's
- * rows) when the rows are gathered, cap_rows, El, H and I_s otherwise; and on
- * the experts' row counts.  Equal calls give equal bits.
+ * rows) when the rows are gathered, cap_rows, El, H and I_s otherwise; on the
+ * experts' row counts; and on whether an operand (x, h or y, whose sizes go with
+ * x_rows and cap_rows) reaches 4 GiB.  Equal calls give equal bits.
  * workspace: at least moe_ffn_workspace_size(cap_rows, El, H, I_s) bytes,
  * 256-byte aligned (holds the bf16 intermediate h, the tile schedule and the
  * split-K partials; its size depends on the current device's compute unit
